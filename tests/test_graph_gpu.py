@@ -70,6 +70,7 @@ def _replay_and_check(run_into, fresh_outputs, w, idx2, stream, label):
         torch.cuda.synchronize()
         for o in captured:
             o.fill_(float("nan"))  # the replay must write every element
+        torch.cuda.synchronize()  # the fill runs on another stream than the replay
         with torch.cuda.stream(stream):  # on the handle's stream, as its calls go
             graph.replay()
         # eager work of the program between replays
