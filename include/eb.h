@@ -42,7 +42,7 @@
  * once that stream has been synchronised.  The other entry points behave the
  * same way.  The handle's tables and settings are fixed at creation; its one
  * piece of mutable device state, the long-bag queue, is used by a lookup and
- * the pass right after it, which each call enqueues under a lock held by the
+ * the kernel right after it, which each call enqueues under a lock held by the
  * handle, so forwards from several host threads may share it.  eb_forward,
  * eb_forward_fm and eb_forward_seq allocate nothing and, outside checked
  * mode, enqueue only kernel launches, so they may be captured into a HIP
@@ -53,25 +53,29 @@
  * one handle whose kernels run at the same time race on its queue.
  *
  * Long bags (Abstract, Sec. IV-A.3: jagged inputs with long-tailed bag
- * lengths).  A bag of more than 1024 lookups would keep one wavefront busy
- * long after the others, so the wavefront that holds it queues it instead, in
- * segments of 2048 positions, and a second kernel (the long-bag pass) pools
- * the segments on many workgroups: each stages a segment's indices (and
- * weights) in LDS and splits it over four wavefronts; the segments' partial
- * sums are added in segment order, so the result is deterministic (its
- * summation order differs from the one-wavefront order, within the same
- * error bound).  On MI355X a bag of a million lookups takes 0.13 ms so,
- * against 30 ms on one wavefront.  The second kernel costs a few
- * microseconds per call even when no bag is long (1.7-6 us on MI355X), so
- * by default it runs only for batches of
- * at least 2^23 lookups (numel(indices) >= 8388608), where that is under 1%
- * of the lookup, and for batches of at least 64 lookups per bag on average
- * (numel(indices) >= 64 * T * B), which are the ones that hold bags of
- * thousands; EB_LONG_BAG (below) turns it on for every batch.  The queue
- * lives in the handle: up to 16384 segments per call with one partial row of
- * the widest table each (at most 64 MiB; 8 MiB for rows of 128 values); the
- * bags whose segments do not fit are pooled by their own wavefront.  With no
- * long bag the pass's workgroups find the queue empty and exit.
+ * lengths).  A bag of thousands of lookups would keep one wavefront busy long
+ * after the others.
+ *   - A batch of at least 64 lookups per bag on average (numel(indices) >=
+ *     64 * T * B) is cut into up to 4096 equal spans of the index stream, one
+ *     per wavefront; a second kernel adds the partial sums of the bags that
+ *     cross spans.  On MI355X 2.3 million lookups in bags of 500 on average
+ *     take 0.045 ms so, against 0.23 ms by the queue below.
+ *   - In other batches, where the long-bag pass runs, a wavefront that holds a
+ *     bag of more than 1024 lookups queues it instead, in segments of 2048
+ *     positions, and a second kernel (the long-bag pass) pools the segments on
+ *     many workgroups: each stages a segment's indices (and weights) in LDS
+ *     and splits it over four wavefronts; the segments' partial sums are added
+ *     in segment order.  The second kernel costs a few microseconds per call
+ *     even when no bag is long (1.7-6 us on MI355X), so by default it runs
+ *     only for batches of at least 2^23 lookups (numel(indices) >= 8388608),
+ *     where that is under 1% of the lookup; EB_LONG_BAG (below) turns it on
+ *     for every batch.
+ * Both give a deterministic result (the summation order differs from the
+ * one-wavefront order, within the same error bound).  Their partial rows live
+ * in the handle: up to 16384 of the widest table each (at most 64 MiB; 8 MiB
+ * for rows of 128 values).  Bags whose segments do not fit the queue are
+ * pooled by their own wavefront; with no long bag the pass's workgroups find
+ * the queue empty and exit.
  *
  * Errors.  Every error the host can detect from the arguments is returned
  * before anything is enqueued, and `out` is left untouched.  The kernel never
@@ -102,12 +106,14 @@
  * threads of that many elements (default: chosen per call from the number of
  * lookups and how many of the sort's workgroups the GPU holds at once).
  * EB_LONG_BAG=n (n > 0) runs the long-bag pass for every batch, for bags of
- * more than n lookups (without it: n = 1024, for the batches above);
- * EB_LONG_BAG=0 turns the pass off (every bag is pooled by one wavefront,
+ * more than n lookups (without it: n = 1024, for the batches above; batches
+ * of at least 64 lookups per bag take the spans instead unless n differs from
+ * 1024);
+ * EB_LONG_BAG=0 turns both off (every bag is pooled by one wavefront,
  * no second kernel, no queue).  EB_LONG_SEG=s (a
  * power of two from 64 to 2048, default 2048) sets the positions per segment.
- * Results do not depend on any of these, except that the long-bag pass
- * changes the order of a long bag's sum (within the same error bound).
+ * Results do not depend on any of these, except that the spans and the
+ * long-bag pass change the order of a bag's sum (within the same error bound).
  */
 #ifndef EB_H_
 #define EB_H_

@@ -49,7 +49,8 @@ constexpr int32_t kRemapMaxTables = 32;
 // segments of up to kLongSegMax positions spread over its workgroups.
 constexpr int64_t kDefaultLongBag = 1024;
 // Without EB_LONG_BAG the pass runs for batches of at least this many
-// lookups, or of at least this many lookups per bag on average.
+// lookups; batches of at least kLongPassMinMean lookups per bag on average
+// take the span kernel instead.
 constexpr int64_t kLongPassMinLookups = (int64_t)1 << 23;
 constexpr int64_t kLongPassMinMean = 64;
 constexpr int32_t kDefaultLongSeg = 2048;          // positions per segment

@@ -23,14 +23,17 @@
 //   * a handle whose tables share one (storage type, LPR) kind launches a body
 //     specialised for it; otherwise one launch per storage type switches on
 //     each table's LPR;
-//   * bags longer than a threshold (1024 lookups unless EB_LONG_BAG says
+//   * a batch of long bags (64 lookups per bag or more on average) is cut into
+//     equal spans of the index stream instead, one per wavefront, and a second
+//     kernel adds the partial sums of the bags that cross spans;
+//   * in other batches, bags longer than a threshold (1024 lookups unless EB_LONG_BAG says
 //     otherwise) are queued by the wavefront that holds them and pooled by a
 //     second kernel, cut into segments that run on many workgroups, each
 //     segment's indices staged in LDS and split over four wavefronts; the
 //     segments' partial sums are added in segment order.  By default this
 //     runs for batches of at least 2^23 lookups (below, the second kernel's
-//     launch would cost more than 1% of the lookup) or of 64 lookups per bag
-//     on average, and for any batch when EB_LONG_BAG is set.
+//     launch would cost more than 1% of the lookup), and for any batch when
+//     EB_LONG_BAG is set.
 // Rows wider than 1 KiB take several 1 KiB column passes.  This file also
 // holds the C ABI's handle creation and the checks shared by the entry points
 // that pool.
@@ -42,6 +45,14 @@
 namespace eb {
 namespace {
 
+// Batches of at least kLongPassMinMean lookups per bag on average take the
+// span kernel, cut into at most kMaxSpans spans of at least kMinSpan positions.
+// The kernel holds 4 to 8 waves per SIMD; about 4 of them, resident together,
+// were fastest (MI355X, 2.3 M lookups in 4 662 bags of 500 on average, int8
+// rows of 64: 2 048 spans 53 us, 3 072 48, 4 096 45, 8 192 49).
+constexpr int64_t kMinSpan = 256;
+constexpr int64_t kMaxSpans = 4096;
+constexpr int32_t kSpanManyPartials = 128;  // a bag of more partial rows is finished by a workgroup
 constexpr int kMaxAutoBagsPerWave = 8;  // cap of the lookup's own choice of bags per wavefront
 
 struct FwdArgs {
@@ -69,6 +80,9 @@ struct FwdArgs {
   int64_t long_len;          // bags with more lookups are queued for the long-bag pass
   int32_t seg_log2;          // that pass pools them in segments of 2^seg_log2 positions
   LongQueue lq;              // the handle's queue (cap 0: no long-bag pass)
+  int64_t span;              // span kernel: positions per wavefront, a multiple of 64
+  int32_t num_spans;
+  int32_t max_passes;        // span kernel: 1 KiB column passes of the widest row
 };
 
 // Pool bags [g0, g0 + nb) of one table (batch rows b0 ..) over the 1 KiB column
@@ -510,6 +524,340 @@ __global__ __launch_bounds__(kBlock) void eb_long_pass_kernel(FwdArgs a) {
   }
 }
 
+// ----------------------------------------------------------------------------
+// Spans.  Where bags hold many lookups on average, a wavefront per bag leaves
+// the GPU to a few long streams.  The span kernel cuts the index stream itself
+// into equal spans, one per wavefront, whatever bags they fall in:
+//   * a wavefront finds the bag its span starts in (a 64-way search of the
+//     offsets, while the span's first indices load), then walks the span as
+//     one stream of chunks, each inside one bag, the next chunk's indices
+//     loaded before the current chunk's rows are gathered.  It holds 64
+//     offsets, one per lane, and steps over empty bags by counting lanes;
+//   * a bag inside the span is stored at once.  The part of a bag that
+//     entered from the span before goes to partial row 2w (w: the span), that
+//     of a bag which starts here and goes on to 2w + 1, and bag[w] names the
+//     latter (kNoBag: none);
+//   * the fix-up kernel adds each such bag's partial rows in an order fixed by
+//     their number, one workgroup per span, and zero-fills the empty bags
+//     (checking the partition as it reads the offsets).
+// No queue, counter or fence.  The long-bag pass's 256 workgroups, its fence
+// and atomics per segment and a wavefront per bag below took 226 us for
+// 2.3 M lookups in 4 662 lognormal bags (mean 500, int8 rows of 64 values);
+// the two kernels here take 45 us.  Every wavefront streams the same number of
+// positions, so what bounds it is the issue of the row gather.
+
+// offsets[g0 + lane] for a window of 64 bags (lanes past the last offset: the
+// largest value, which no position reaches)
+__device__ __forceinline__ int64_t offset_window(const FwdArgs &a, int32_t g0) {
+  const int64_t i = (int64_t)g0 + (threadIdx.x & (kWave - 1));
+  const int64_t j = i <= a.num_bags ? i : a.num_bags;
+  const int64_t v = a.idx64 ? static_cast<const int64_t *>(a.offsets)[j]
+                            : (int64_t) static_cast<const int32_t *>(a.offsets)[j];
+  return i <= a.num_bags ? v : INT64_MAX;
+}
+
+// First bag of a window that holds the last offset <= pos (by steps of 64
+// probes; any content of the offsets ends in a window inside them).
+__device__ __forceinline__ int32_t search_offsets(const FwdArgs &a, int64_t pos) {
+  const int lane = threadIdx.x & (kWave - 1);
+  int64_t lo = 0, range = (int64_t)a.num_bags + 1;
+  while (range > kWave) {
+    const int64_t step = (range + kWave - 1) / kWave;
+    const int64_t i = lo + lane * step;
+    const int64_t j = i <= a.num_bags ? i : a.num_bags;
+    const int64_t v = a.idx64 ? static_cast<const int64_t *>(a.offsets)[j]
+                              : (int64_t) static_cast<const int32_t *>(a.offsets)[j];
+    const int c = __builtin_popcountll(__ballot(i <= a.num_bags && v <= pos));
+    lo += (c > 0 ? c - 1 : 0) * step;
+    range = step;
+  }
+  return (int32_t)lo;
+}
+
+template <int DT, int LPR, bool W>
+__device__ __forceinline__ void span_store(const TableMeta &m, const FwdArgs &a, int col_base, float (&acc)[Vals<DT>::n],
+                                           float *row, int64_t mean_len) {
+  using R = Reduce<DT, LPR>;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int colb = col_base + (lane % LPR) * 16;
+  R::run(acc);
+  if (R::stores(lane) && colb < m.code_bytes) {
+    const int f = R::first_value(lane);
+    float outv[R::KEEP];
+#pragma unroll
+    for (int i = 0; i < R::KEEP; ++i) outv[i] = acc[i];
+    if (mean_len > 0) {
+      const float fl = (float)mean_len;
+#pragma unroll
+      for (int i = 0; i < R::KEEP; ++i) outv[i] = outv[i] / fl;
+    }
+    store_slice<R::KEEP>(row + colb / Vals<DT>::esize + f, outv);
+  }
+}
+
+#define EB_SPAN_LPR(LOG2_, CALL) \
+  case LOG2_: {                  \
+    constexpr int LPR = 1 << (LOG2_); \
+    CALL;                        \
+  } break;
+#define EB_SPAN_SWITCH(CALL)                                                                              \
+  if constexpr (LOG2 >= 0) {                                                                              \
+    constexpr int LPR = 1 << (LOG2 >= 0 ? LOG2 : 0);                                                      \
+    CALL;                                                                                                 \
+  } else {                                                                                                \
+    switch (m.kind % 8) {                                                                                 \
+      EB_SPAN_LPR(0, CALL) EB_SPAN_LPR(1, CALL) EB_SPAN_LPR(2, CALL) EB_SPAN_LPR(3, CALL)                 \
+      EB_SPAN_LPR(4, CALL) EB_SPAN_LPR(5, CALL) EB_SPAN_LPR(6, CALL)                                      \
+      default: break;                                                                                     \
+    }                                                                                                     \
+  }
+
+// One 1 KiB column pass over span w.
+template <int DT, int LOG2, bool W>
+__device__ __forceinline__ void span_walk(const FwdArgs &a, int32_t w, int pass) {
+  constexpr int V = Vals<DT>::n;
+  constexpr bool SPLIT = EB_INT8_SPLIT_BIAS && DT == kU8 && !W;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t p0 = (int64_t)w * a.span;
+  const int64_t p1 = p0 + a.span < a.num_indices ? p0 + a.span : a.num_indices;
+  const int col_base = pass * kPassBytes;
+
+  int64_t c = p0;
+  RawChunk cur = load_chunk<W>(a.indices, a.weights, a.idx64, c, p1);
+  int32_t g0 = search_offsets(a, p0);
+  int64_t off = offset_window(a, g0);
+
+  // the bag that holds position pos: its number, first position and end;
+  // false when no bag does (offsets that are no partition)
+  int32_t g = -1;
+  int64_t lo = 0, hi = 0;
+  auto find = [&](int64_t pos) -> bool {
+    int n = __builtin_popcountll(__ballot(off <= pos));
+    if (n == kWave) {  // past the window: the next one, or a new search
+      g0 += kWave - 1;
+      off = offset_window(a, g0);
+      n = __builtin_popcountll(__ballot(off <= pos));
+      if (n == kWave) {
+        g0 = search_offsets(a, pos);
+        off = offset_window(a, g0);
+        n = __builtin_popcountll(__ballot(off <= pos));
+      }
+    }
+    if (n == 0 || n == kWave || g0 + n - 1 >= a.num_bags) return false;
+    g = g0 + n - 1;
+    lo = readlane64(off, n - 1);
+    hi = readlane64(off, n);
+    hi = hi < a.num_indices ? hi : a.num_indices;
+    return lo >= 0 && hi > pos;
+  };
+
+  float acc[V];
+  float cb = 0.0f;
+#pragma unroll
+  for (int i = 0; i < V; ++i) acc[i] = 0.0f;
+  bool in_bag = find(c);
+  int32_t t = -1;
+  TableMeta m;
+  while (in_bag) {
+    const int32_t tn = g / a.batch;
+    if (tn != t) {
+      t = tn;
+      m = a.meta[t];
+    }
+    const int32_t bag = g;
+    const int64_t blo = lo, bhi = hi;
+    const int64_t e = bhi < p1 ? bhi : p1;
+    cur.n = (int)(e - c < kWave ? e - c : kWave);
+    const bool last = c + kWave >= e;
+    const int64_t cn = last ? e : c + kWave;
+    const bool more = cn < p1;
+    RawChunk nxt;
+    if (more) nxt = load_chunk<W>(a.indices, a.weights, a.idx64, cn, p1);
+    if (last) in_bag = more && find(cn);
+
+    if (m.kind / 8 == DT && pass < m.passes) {
+      const Chunk k = resolve(cur, m.num_rows, a.idx64);
+      const int colb0 = col_base;
+      EB_SPAN_SWITCH((gather_chunk<DT, LPR, W, SPLIT>(m, a.ctx, k, acc, cb, colb0 + (lane % LPR) * 16,
+                                                      colb0 + (lane % LPR) * 16 < m.code_bytes)));
+      if (last) {
+        if constexpr (SPLIT) {
+#pragma unroll
+          for (int i = 0; i < V; ++i) acc[i] += cb;
+          cb = 0.0f;
+        }
+        const bool whole = blo >= p0 && bhi <= p1;
+        float *row = whole ? a.out + (int64_t)(bag - t * a.batch) * a.out_ld + m.out_col
+                           : a.lq.part + ((int64_t)2 * w + (blo >= p0 ? 1 : 0)) * a.lq.part_ld;
+        EB_SPAN_SWITCH((span_store<DT, LPR, W>(m, a, colb0, acc, row, whole && a.mean ? bhi - blo : 0)));
+#pragma unroll
+        for (int i = 0; i < V; ++i) acc[i] = 0.0f;
+      }
+    }
+    if (last && !in_bag) {
+      // the span's last bag: does it go on, and did it start here?
+      if (pass == 0 && lane == 0) a.lq.bag[w] = (bhi > p1 && blo >= p0) ? (uint32_t)bag : kNoBag;
+      return;
+    }
+    c = cn;
+    cur = nxt;
+  }
+  if (pass == 0 && lane == 0) a.lq.bag[w] = kNoBag;
+}
+
+template <int DT, int LOG2, bool W>
+__global__ __launch_bounds__(kWave) void eb_span_kernel(FwdArgs a) {
+  const uint32_t blk = a.xcd_remap ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int32_t w = (int32_t)blk;
+  if (w >= a.num_spans) return;
+  for (int p = 0; p < a.max_passes; ++p) span_walk<DT, LOG2, W>(a, w, p);
+}
+
+#undef EB_SPAN_SWITCH
+#undef EB_SPAN_LPR
+
+// Finishes the bags that cross spans: wavefront w the one that starts in span
+// w and goes on past it (if any).  `lanes` consecutive threads from thread 0
+// of the group (a wavefront, or the whole workgroup for a bag of many spans)
+// take 4 columns each of a 256-column window, L lanes to a row, and add
+// interleaved partial rows, eight loads in flight.
+__device__ __forceinline__ void span_partials(const FwdArgs &a, int32_t w, int32_t K, int L, int tid, int lanes, int col,
+                                              bool ok, float (&s)[4]) {
+  const int groups = lanes / L;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s[i] = 0.0f;
+  if (!ok) return;
+  for (int32_t k = tid / L; k < K; k += 8 * groups) {
+    f32x4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int32_t q = k + u * groups < K ? k + u * groups : k;
+      v[u] = *(const EB_GLOBAL f32x4 *)(a.lq.part + ((int64_t)2 * (w + q) + (q == 0 ? 1 : 0)) * a.lq.part_ld + col);
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (k + u * groups < K) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] += v[u][i];
+      }
+    }
+  }
+}
+
+__device__ __forceinline__ void span_finish(const FwdArgs &a, float (&s)[4], int64_t len, float *dst) {
+  if (a.mean && len > 0) {
+    const float fl = (float)len;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s[i] = s[i] / fl;
+  }
+  store_slice<4>(dst, s);
+}
+
+__global__ __launch_bounds__(kBlock) void eb_span_fixup_kernel(FwdArgs a) {
+  __shared__ float s_part[4 * kBlock];
+  __shared__ int32_t s_many[kWavesPerBlock];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int32_t w0 = (int32_t)blockIdx.x * kWavesPerBlock;
+  // the span's bag, its partial rows K and its output
+  struct Crossing {
+    int32_t K, dim;
+    int64_t len;
+    float *dst;
+  };
+  auto crossing = [&](int32_t w) {
+    Crossing c = {0, 0, 0, nullptr};
+    const uint32_t gu = w < a.num_spans ? __builtin_amdgcn_readfirstlane(a.lq.bag[w]) : kNoBag;
+    if (gu < (uint32_t)a.num_bags) {
+      int64_t lo, hi;
+      long_bag_range(a, gu, lo, hi);
+      const int64_t last = hi > lo ? (hi - 1) / a.span : w;
+      c.K = (int32_t)(last < w ? 1 : (last < a.num_spans ? last - w + 1 : a.num_spans - w));
+      const int32_t t = (int32_t)(gu / (uint32_t)a.batch);
+      const int32_t b = (int32_t)(gu - (uint32_t)t * (uint32_t)a.batch);
+      c.dim = a.meta[t].dim;
+      c.len = hi - lo;
+      c.dst = a.out + (int64_t)b * a.out_ld + a.meta[t].out_col;
+    }
+    return c;
+  };
+  const Crossing mine = crossing(w0 + wave);
+  const bool many = mine.K > kSpanManyPartials;
+  if (lane == 0) s_many[wave] = many ? 1 : 0;
+  if (mine.K > 0 && !many) {
+    int L = 1;
+    while (L < kWave && 4 * L < mine.dim) L <<= 1;
+    for (int cw = 0; cw < mine.dim; cw += 4 * kWave) {
+      const int col = cw + 4 * (lane % L);
+      const bool ok = col < mine.dim;
+      float s[4];
+      span_partials(a, w0 + wave, mine.K, L, lane, kWave, col, ok, s);
+      for (int q = 1; q < kWave / L; ++q) {  // the groups' sums, in group order
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float o = __shfl(s[i], lane % L + q * L);
+          if (lane < L) s[i] += o;
+        }
+      }
+      if (lane < L && ok) span_finish(a, s, mine.len, mine.dst + col);
+    }
+  }
+  __syncthreads();
+  for (int j = 0; j < kWavesPerBlock; ++j) {
+    if (!__builtin_amdgcn_readfirstlane(s_many[j])) continue;
+    const Crossing c = crossing(w0 + j);
+    int L = 1;
+    while (L < kWave && 4 * L < c.dim) L <<= 1;
+    for (int cw = 0; cw < c.dim; cw += 4 * kWave) {
+      const int col = cw + 4 * (threadIdx.x % L);
+      const bool ok = col < c.dim;
+      float s[4];
+      span_partials(a, w0 + j, c.K, L, threadIdx.x, kBlock, col, ok, s);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s_part[threadIdx.x * 4 + i] = s[i];
+      __syncthreads();
+      if ((int)threadIdx.x < L && ok) {
+        for (int q = 1; q < kBlock / L; ++q) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) s[i] += s_part[(q * L + threadIdx.x) * 4 + i];
+        }
+        span_finish(a, s, c.len, c.dst + col);
+      }
+      __syncthreads();  // s_part is reused by the next window
+    }
+  }
+  // zero-fill the empty bags of every 64-bag window
+  const int64_t waves = (int64_t)gridDim.x * kWavesPerBlock;
+  for (int64_t base = ((int64_t)w0 + wave) * kWave; base < a.num_bags; base += waves * kWave) {
+    const int64_t g = base + lane;
+    const bool in = g < a.num_bags;
+    const int64_t gg = in ? g : a.num_bags - 1;
+    int64_t lo, hi;
+    if (a.idx64) {
+      lo = static_cast<const int64_t *>(a.offsets)[gg];
+      hi = static_cast<const int64_t *>(a.offsets)[gg + 1];
+    } else {
+      lo = static_cast<const int32_t *>(a.offsets)[gg];
+      hi = static_cast<const int32_t *>(a.offsets)[gg + 1];
+    }
+    const bool bad = lo < 0 || hi < lo || hi > a.num_indices || (gg == 0 && lo != 0) ||
+                     (gg == a.num_bags - 1 && hi != a.num_indices);
+    if (__ballot(bad) && lane == 0) atomicOr(a.ctx.err, kErrOffsets);
+    uint64_t empty = __ballot(in && hi <= lo);
+    while (empty) {
+      const int64_t e = base + __builtin_ctzll(empty);
+      empty &= empty - 1;
+      const int32_t t = (int32_t)(e / a.batch);
+      const TableMeta &m = a.meta[t];
+      float *dst = a.out + (e - (int64_t)t * a.batch) * a.out_ld + m.out_col;
+      for (int col = 4 * lane; col < m.dim; col += 4 * kWave) {
+        const float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        store_slice<4>(dst + col, z);
+      }
+    }
+  }
+}
+
 typedef void (*KernelFn)(FwdArgs);
 
 // kernel for (storage type, log2 lanes per row or -1, weighted)
@@ -531,6 +879,26 @@ KernelFn pick_kernel(int dt, int log2, bool weighted) {
   if (dt == kF32) return weighted ? pick_kernel<kF32, true>(log2) : pick_kernel<kF32, false>(log2);
   if (dt == kF16) return weighted ? pick_kernel<kF16, true>(log2) : pick_kernel<kF16, false>(log2);
   return weighted ? pick_kernel<kU8, true>(log2) : pick_kernel<kU8, false>(log2);
+}
+
+template <int DT, bool W>
+KernelFn pick_span_kernel(int log2) {
+  switch (log2) {
+    case 0: return eb_span_kernel<DT, 0, W>;
+    case 1: return eb_span_kernel<DT, 1, W>;
+    case 2: return eb_span_kernel<DT, 2, W>;
+    case 3: return eb_span_kernel<DT, 3, W>;
+    case 4: return eb_span_kernel<DT, 4, W>;
+    case 5: return eb_span_kernel<DT, 5, W>;
+    case 6: return eb_span_kernel<DT, 6, W>;
+    default: return eb_span_kernel<DT, -1, W>;
+  }
+}
+
+KernelFn pick_span_kernel(int dt, int log2, bool weighted) {
+  if (dt == kF32) return weighted ? pick_span_kernel<kF32, true>(log2) : pick_span_kernel<kF32, false>(log2);
+  if (dt == kF16) return weighted ? pick_span_kernel<kF16, true>(log2) : pick_span_kernel<kF16, false>(log2);
+  return weighted ? pick_span_kernel<kU8, true>(log2) : pick_span_kernel<kU8, false>(log2);
 }
 
 KernelFn pick_long_kernel(int dt, bool weighted) {
@@ -575,6 +943,32 @@ eb_status check_forward_args(const eb_tables *h, const eb_tensor &indices, const
   return EB_OK;
 }
 
+// The span kernel and its fix-up (arguments filled in by launch_forward).
+static hipError_t launch_spans(const eb_tables *h, FwdArgs &a, const FwdShape &sh) {
+  a.lq.cap = 0;
+  const int64_t most = h->lq.cap / 2 < kMaxSpans ? h->lq.cap / 2 : kMaxSpans;
+  int64_t span = (a.num_indices + most - 1) / most;
+  span = (span + kWave - 1) / kWave * kWave;
+  a.span = span < kMinSpan ? kMinSpan : span;
+  a.num_spans = (int32_t)((a.num_indices + a.span - 1) / a.span);
+  a.max_passes = 1;
+  for (int32_t t = 0; t < h->num_tables; ++t)
+    a.max_passes = h->h_meta[t].passes > a.max_passes ? h->h_meta[t].passes : a.max_passes;
+  hipError_t e = hipSuccess;
+  std::lock_guard<std::mutex> lock(*h->enqueue);
+  for (int dt = 0; dt < 3 && e == hipSuccess; ++dt) {
+    if (!(h->dtype_mask & (1 << dt))) continue;
+    hipLaunchKernelGGL(pick_span_kernel(dt, h->single_log2, sh.weighted), dim3((unsigned)a.num_spans), dim3(kWave), 0,
+                       h->stream, a);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(eb_span_fixup_kernel, dim3((unsigned)((a.num_spans + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(kBlock), 0, h->stream, a);
+    e = hipGetLastError();
+  }
+  return e;
+}
+
 hipError_t launch_forward(const eb_tables *h, const eb_tensor &indices, const eb_tensor &offsets,
                           const eb_tensor &weights, eb_pooling pooling, const eb_tensor &out, const FwdShape &sh) {
   FwdArgs a;
@@ -593,12 +987,8 @@ hipError_t launch_forward(const eb_tables *h, const eb_tensor &indices, const eb
   // The pass costs one more kernel on the stream whether or not a bag needs
   // it (on MI355X 1.7-6 us: 8% of a 23 us lookup of a million lookups in
   // bags of twenty, under 1% from about eight million lookups), so unless
-  // the handle asked for it (EB_LONG_BAG set) it runs for batches that large,
-  // and for batches whose bags hold kLongPassMinMean lookups or more on
-  // average: bag lengths are long-tailed, so those are the batches that hold
-  // bags of thousands.
-  const bool long_pass = h->lq.cap > 0 && (h->long_bag_forced || indices.numel >= kLongPassMinLookups ||
-                                           indices.numel >= kLongPassMinMean * sh.num_bags);
+  // the handle asked for it (EB_LONG_BAG set) it runs for batches that large.
+  const bool long_pass = h->lq.cap > 0 && (h->long_bag_forced || indices.numel >= kLongPassMinLookups);
   if (!long_pass) a.lq.cap = 0;  // the lookup queues nothing: every bag is its wavefront's
   a.num_indices = indices.numel;
   a.out_ld = h->sum_dim;
@@ -606,6 +996,13 @@ hipError_t launch_forward(const eb_tables *h, const eb_tensor &indices, const eb
   a.batch = (int32_t)sh.batch;
   a.idx64 = indices.elem_type == EB_I64;
   a.mean = pooling == EB_POOL_MEAN;
+
+  // Long bags throughout: spans, unless EB_LONG_BAG asks for another threshold
+  // than the default (then the bags above it go through the queue).
+  if (h->lq.cap >= 2 && (!h->long_bag_forced || h->long_bag_len == kDefaultLongBag) &&
+      indices.numel >= kLongPassMinMean * sh.num_bags && indices.numel > 0)
+    return launch_spans(h, a, sh);
+
   int64_t k = h->bags_per_wave;
   if (k == 0) {
     // More bags per wavefront hide more latency (each bag's indices arrive
