@@ -106,6 +106,17 @@ struct TableMeta {
 typedef const EB_GLOBAL unsigned char gbyte;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16), aligned(8)));
+
+// Table t's descriptor (t wave-uniform).  Descriptors never change, so they
+// are read from the constant address space: into scalar registers, also where
+// the kernel has stored to memory before (the compiler would otherwise load
+// them into vector registers, and loop over lanes at every buffer load).
+__device__ __forceinline__ TableMeta table_meta(const TableMeta *meta, int32_t t) {
+  static_assert(sizeof(TableMeta) == sizeof(u32x16), "one vector holds a descriptor");
+  typedef const __attribute__((address_space(4))) u32x16 cvec;
+  return __builtin_bit_cast(TableMeta, *(cvec *)(uintptr_t)(meta + __builtin_amdgcn_readfirstlane(t)));
+}
 // same vector, only 4-byte aligned: int8 rows of D+4 bytes start on any dword
 typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -300,6 +311,142 @@ __device__ __forceinline__ void store_slice(float *dst, const float (&v)[KEEP]) 
   }
 }
 
+// Where a row's bytes are.  Each lane works out the address of the row at its
+// own position once per chunk, and a gather step hands it to the row's lanes
+// by a cross-lane permute, so a step costs one permute and one add per load
+// and nothing separates the loads of a batch.  (With the row number permuted
+// instead and its address formed, range-checked and replaced by an all-zero
+// row at every step, a step took thirteen vector and scalar instructions and
+// the batch's permutes waited for each other: 64 int8 tables of 128 values at
+// batch 65 536 took 2.81 ms against 2.73, 26 fp32 tables of 64 at batch 2048
+// 24.8 us against 23.7, 8 fp16 tables of 128 at batch 16 384 83.3 against 79.8.)
+//
+// Tables of up to kMaxBufferBytes (BIG false) are read through buffer
+// resources: an address is a 32-bit offset, and the offset kNoOffset of a row
+// that does not exist is past the buffer's end, where a buffer load gives
+// zero and reads nothing.  A handle with a larger table (BIG) uses 64-bit
+// addresses, and the handle's all-zero row for rows that do not exist.
+constexpr uint32_t kNoOffset = 0xFFFF0000u;  // plus a column byte (< 32 KiB) it does not wrap
+constexpr int64_t kMaxBufferBytes = kNoOffset;
+constexpr int kBufferFlags = 0x00020000;  // untyped data
+
+template <bool BIG>
+struct RowAddr;  // of a lane's row and of its scale/bias word (int8)
+template <>
+struct RowAddr<false> {
+  uint32_t row, sb;
+};
+template <>
+struct RowAddr<true> {
+  uint64_t row, sb;
+};
+
+template <int DT, bool BIG>
+struct RowSource;
+template <int DT>
+struct RowSource<DT, false> {
+  __amdgpu_buffer_rsrc_t rows, words;
+  uint32_t stride, sb_stride;
+  __device__ __forceinline__ RowSource(const TableMeta &m, const GatherCtx &) : stride(m.row_stride), sb_stride(m.sb_stride) {
+    rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(m.data), 0, m.num_rows * (int)m.row_stride,
+                                             kBufferFlags);
+    if constexpr (DT == kU8)
+      words = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(m.sb_base), 0, m.num_rows * (int)m.sb_stride,
+                                                kBufferFlags);
+  }
+  __device__ __forceinline__ RowAddr<false> locate(uint32_t row) const {
+    RowAddr<false> r;
+    r.row = row == kBadRow ? kNoOffset : row * stride;
+    r.sb = DT == kU8 ? (row == kBadRow ? kNoOffset : row * sb_stride) : 0u;
+    return r;
+  }
+  __device__ __forceinline__ u32x4 load_row(uint32_t at, int colb) const {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, at + (uint32_t)colb, 0, 0));
+  }
+  __device__ __forceinline__ uint32_t load_word(uint32_t at) const {
+    return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(words, at, 0, 0);
+  }
+};
+template <int DT>
+struct RowSource<DT, true> {
+  const unsigned char *data, *sb_base, *zero;
+  uint32_t stride, sb_stride;
+  __device__ __forceinline__ RowSource(const TableMeta &m, const GatherCtx &a)
+      : data(m.data), sb_base(m.sb_base), zero(a.zero), stride(m.row_stride), sb_stride(m.sb_stride) {}
+  __device__ __forceinline__ RowAddr<true> locate(uint32_t row) const {
+    RowAddr<true> r;
+    r.row = reinterpret_cast<uint64_t>(row == kBadRow ? zero : data + (uint64_t)row * stride);
+    r.sb = DT == kU8 ? reinterpret_cast<uint64_t>(row == kBadRow ? zero : sb_base + (uint64_t)row * sb_stride) : 0u;
+    return r;
+  }
+  __device__ __forceinline__ u32x4 load_row(uint64_t at, int colb) const {
+    return load_slice<DT>((gbyte *)(at + (uint64_t)colb));
+  }
+  __device__ __forceinline__ uint32_t load_word(uint64_t at) const { return *(const EB_GLOBAL uint32_t *)at; }
+};
+
+// Lane `l`'s value on every lane (l differs from lane to lane).
+__device__ __forceinline__ uint32_t from_lane(uint32_t v, int l) { return (uint32_t)__shfl((int)v, l); }
+__device__ __forceinline__ uint64_t from_lane(uint64_t v, int l) {
+  return ((uint64_t)from_lane((uint32_t)(v >> 32), l) << 32) | from_lane((uint32_t)v, l);
+}
+// The same for an l that every lane shares.
+__device__ __forceinline__ uint32_t from_lane_uniform(uint32_t v, int l) { return __builtin_amdgcn_readlane(v, l); }
+__device__ __forceinline__ uint64_t from_lane_uniform(uint64_t v, int l) { return (uint64_t)readlane64((int64_t)v, l); }
+
+// Gather steps [s0, s0 + N) of one chunk (RPL rows per step) and add them into
+// this lane's accumulators.  Lanes past the chunk's end hold the address of no
+// row, which adds zeros.  colb: the lane's column byte, 0 where its slice lies
+// past the row's end (it then reads what is never stored).
+template <int DT, int LPR, bool W, bool SPLIT, int N, bool BIG>
+__device__ __forceinline__ void gather_rows(const RowSource<DT, BIG> &src, const RowAddr<BIG> &at, const GatherCtx &a,
+                                            float wt, int s0, float (&acc)[Vals<DT>::n], float &cb, int colb) {
+  constexpr int RPL = kWave / LPR;
+  const int grp = (threadIdx.x & (kWave - 1)) / LPR;
+  u32x4 v[N];
+  uint32_t sb[N];
+  float w[N];
+  if constexpr (RPL == 1) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      v[u] = src.load_row(from_lane_uniform(at.row, s0 + u), colb);
+      sb[u] = DT == kU8 ? src.load_word(from_lane_uniform(at.sb, s0 + u)) : 0u;
+      w[u] = W ? __uint_as_float(from_lane_uniform(__float_as_uint(wt), s0 + u)) : 1.0f;
+    }
+  } else {
+    decltype(at.row) ar[N], as[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int r = (s0 + u) * RPL + grp;
+      ar[u] = from_lane(at.row, r);
+      if constexpr (DT == kU8) as[u] = from_lane(at.sb, r);
+      w[u] = W ? __uint_as_float(from_lane(__float_as_uint(wt), r)) : 1.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      v[u] = src.load_row(ar[u], colb);
+      sb[u] = 0u;
+      if constexpr (DT == kU8) sb[u] = src.load_word(as[u]);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < N; ++u) accumulate<DT, W, SPLIT>(acc, cb, v[u], sb[u], w[u], a.one);
+}
+
+// One straight-line batch of exactly `rem` steps (1 <= rem <= N).
+template <int DT, int LPR, bool W, bool SPLIT, int N, bool BIG>
+__device__ __forceinline__ void gather_rows_exact(int rem, const RowSource<DT, BIG> &src, const RowAddr<BIG> &at,
+                                                  const GatherCtx &a, float wt, int s, float (&acc)[Vals<DT>::n],
+                                                  float &cb, int colb) {
+  if constexpr (N > 0) {
+    if (rem == N) {
+      gather_rows<DT, LPR, W, SPLIT, N, BIG>(src, at, a, wt, s, acc, cb, colb);
+      return;
+    }
+    gather_rows_exact<DT, LPR, W, SPLIT, N - 1, BIG>(rem, src, at, a, wt, s, acc, cb, colb);
+  }
+}
+
 // Gather steps [s0, s0 + N) of one chunk (RPL rows per step) and add them into
 // this lane's accumulators.  Straight-line code: a lane whose row does not
 // exist (past the chunk's end, outside the table, or a slice past the row's
@@ -340,28 +487,15 @@ __device__ __forceinline__ void gather_steps(const TableMeta &m, const GatherCtx
   for (int u = 0; u < N; ++u) accumulate<DT, W, SPLIT>(acc, cb, v[u], sb[u], w[u], a.one);
 }
 
-// One straight-line batch of exactly `rem` steps (1 <= rem <= N).
-template <int DT, int LPR, bool W, bool SPLIT, int N>
-__device__ __forceinline__ void gather_exact(int rem, const TableMeta &m, const GatherCtx &a, const Chunk &k, int s,
-                                             float (&acc)[Vals<DT>::n], float &cb, int colb, bool colok) {
-  if constexpr (N > 0) {
-    if (rem == N) {
-      gather_steps<DT, LPR, W, SPLIT, N>(m, a, k, s, acc, cb, colb, colok);
-      return;
-    }
-    gather_exact<DT, LPR, W, SPLIT, N - 1>(rem, m, a, k, s, acc, cb, colb, colok);
-  }
-}
-
 // Gather all rows of one chunk: full batches of U steps, then one batch for
 // the rest, so a chunk of up to U steps costs one memory round trip.  With
 // batches of 8 the last one has exactly the remaining steps: padding it to a
-// power of two spent up to 3 of every 8 loads on the zero row (a 20-row bag
-// of 4 rows per load takes 5 steps), which cost 7% on 26 fp32 D64 tables at
-// batch 2048 with Poisson(20) bags.  With batches of 4 it
-// is padded to 2 or 4 steps (at most one padded load): exact sizes there were
-// no faster and took more registers.
-template <int DT, int LPR, bool W, bool SPLIT>
+// power of two spent up to 3 of every 8 loads on rows that do not exist (a
+// 20-row bag of 4 rows per load takes 5 steps), which cost 7% on 26 fp32 D64
+// tables at batch 2048 with Poisson(20) bags.  With batches of 4 it is padded
+// to 2 or 4 steps (at most one padded load): exact sizes there were no faster
+// and took more registers.
+template <int DT, int LPR, bool W, bool SPLIT, bool BIG>
 __device__ __forceinline__ void gather_chunk(const TableMeta &m, const GatherCtx &a, const Chunk &k,
                                              float (&acc)[Vals<DT>::n], float &cb, int colb, bool colok) {
   constexpr int RPL = kWave / LPR;
@@ -370,21 +504,24 @@ __device__ __forceinline__ void gather_chunk(const TableMeta &m, const GatherCtx
   if (__ballot(lane < k.n && k.row == kBadRow)) {
     if (lane == 0) atomicOr(a.err, kErrIndex);
   }
+  const RowSource<DT, BIG> src(m, a);
+  const RowAddr<BIG> at = src.locate(k.row);
+  colb = colok ? colb : 0;
   const int steps = (k.n + RPL - 1) / RPL;
   int s = 0;
   if constexpr (U >= 8) {
-    for (; steps - s >= U; s += U) gather_steps<DT, LPR, W, SPLIT, U>(m, a, k, s, acc, cb, colb, colok);
-    if (steps > s) gather_exact<DT, LPR, W, SPLIT, U - 1>(steps - s, m, a, k, s, acc, cb, colb, colok);
+    for (; steps - s >= U; s += U) gather_rows<DT, LPR, W, SPLIT, U, BIG>(src, at, a, k.w, s, acc, cb, colb);
+    if (steps > s) gather_rows_exact<DT, LPR, W, SPLIT, U - 1, BIG>(steps - s, src, at, a, k.w, s, acc, cb, colb);
   } else {
-    for (; steps - s > U / 2; s += U) gather_steps<DT, LPR, W, SPLIT, U>(m, a, k, s, acc, cb, colb, colok);
+    for (; steps - s > U / 2; s += U) gather_rows<DT, LPR, W, SPLIT, U, BIG>(src, at, a, k.w, s, acc, cb, colb);
     const int rem = steps - s;  // 0 .. U/2
     if constexpr (U >= 4) {
       if (rem > 1) {
-        gather_steps<DT, LPR, W, SPLIT, 2>(m, a, k, s, acc, cb, colb, colok);
+        gather_rows<DT, LPR, W, SPLIT, 2, BIG>(src, at, a, k.w, s, acc, cb, colb);
         return;
       }
     }
-    if (rem > 0) gather_steps<DT, LPR, W, SPLIT, 1>(m, a, k, s, acc, cb, colb, colok);
+    if (rem > 0) gather_rows<DT, LPR, W, SPLIT, 1, BIG>(src, at, a, k.w, s, acc, cb, colb);
   }
 }
 
@@ -576,6 +713,7 @@ struct eb_tables {
   // enqueue them under this lock.
   std::mutex *enqueue;
   int32_t dtype_mask;     // bit d set: some table has storage type d
+  int32_t big_tables;     // some table's rows (or scale/bias words) span more than kMaxBufferBytes
   int32_t single_log2;    // lanes-per-row log2 shared by every table of one type, else -1
   int32_t xcd_remap;      // see xcd_contiguous
   int64_t sum_dim;

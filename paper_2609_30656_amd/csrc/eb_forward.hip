@@ -126,7 +126,7 @@ __device__ __forceinline__ void wave_run(const FwdArgs &a, int32_t w, int32_t &t
   nb = (a.batch - b0) < k ? (a.batch - b0) : k;
 }
 
-template <int DT, int LPR, bool W>
+template <int DT, int LPR, bool W, bool BIG>
 __device__ __forceinline__ void pool_bags(const TableMeta &m, const FwdArgs &a, int32_t g0, int nb, int32_t b0,
                                           int col_base, int64_t my_off, uint32_t queued) {
   // my_off: run_offsets(a, g0, nb); bag j is skipped when bit j of `queued`
@@ -181,7 +181,7 @@ __device__ __forceinline__ void pool_bags(const TableMeta &m, const FwdArgs &a, 
     RawChunk nxt;
     if (more) nxt = load_chunk<W>(a.indices, a.weights, a.idx64, cn, nhi);
 
-    gather_chunk<DT, LPR, W, SPLIT>(m, a.ctx, resolve(cur, m.num_rows, a.idx64), acc, cb, colb, colok);
+    gather_chunk<DT, LPR, W, SPLIT, BIG>(m, a.ctx, resolve(cur, m.num_rows, a.idx64), acc, cb, colb, colok);
 
     if (last) {
       if constexpr (SPLIT) {
@@ -299,38 +299,33 @@ __device__ __forceinline__ uint32_t queue_long_bags(const FwdArgs &a, int32_t g0
   return queued;
 }
 
-template <int DT, int LPR, bool W>
+template <int DT, int LPR, bool W, bool BIG>
 __device__ __forceinline__ void pool_all_passes(const TableMeta &m, const FwdArgs &a, int32_t g0, int nb,
                                                 int32_t b0, int64_t my_off, uint32_t queued) {
   if constexpr (LPR == kWave) {
-    for (int p = 0; p < m.passes; ++p) pool_bags<DT, LPR, W>(m, a, g0, nb, b0, p * kPassBytes, my_off, queued);
+    for (int p = 0; p < m.passes; ++p) pool_bags<DT, LPR, W, BIG>(m, a, g0, nb, b0, p * kPassBytes, my_off, queued);
   } else {
-    pool_bags<DT, LPR, W>(m, a, g0, nb, b0, 0, my_off, queued);
+    pool_bags<DT, LPR, W, BIG>(m, a, g0, nb, b0, 0, my_off, queued);
   }
 }
 
 #define EB_LPR(LOG2)                                                          \
   case LOG2:                                                                  \
-    pool_all_passes<DT, (1 << (LOG2)), W>(m, a, g0, nb, b0, my_off, queued);  \
+    pool_all_passes<DT, (1 << (LOG2)), W, BIG>(m, a, g0, nb, b0, my_off, queued);  \
     break;
 
 // One wavefront per run of bags.  DT is the storage type the launch serves
 // (wavefronts of other tables skip their own bags).  LOG2 >= 0 fixes the
 // lanes per row for handles whose tables all share one kind; LOG2 < 0
 // switches on each table's lanes per row.  Specialising keeps the register
-// count (and so the occupancy) at what that kind needs.  The fp16 and
-// unweighted fp32 kernels that switch over every width are held to 8 waves
-// per SIMD (64 VGPRs), which they meet without spilling; the int8 one would
-// spill, so it keeps the compiler's choice.  The unweighted int8 kernels of
-// one width are held to 8 as well: left alone the compiler gives them 69-72
-// VGPRs (7 waves), held they take 50-60 without spilling, and 64 int8 tables
-// of 128 values at batch 65 536 run 0.7% faster.
-template <int DT, int LOG2, bool W>
+// count (and so the occupancy) at what that kind needs.  Rows read through
+// buffer resources leave every one of these kernels within 64 VGPRs, so all
+// are held to 8 waves per SIMD (the fp16 one of every width would take 70 by
+// itself: 100 mixed fp16 tables 390 us, held 384); with 64-bit row addresses
+// (BIG) some would spill, so those keep the compiler's choice.
+template <int DT, int LOG2, bool W, bool BIG>
 __global__ __launch_bounds__(kWave)
-__attribute__((amdgpu_waves_per_eu(((LOG2 < 0 && (DT == kF16 || (DT == kF32 && !W))) || (DT == kU8 && LOG2 >= 0 && !W))
-                                       ? 8
-                                       : 1,
-                                   8)))
+__attribute__((amdgpu_waves_per_eu(BIG ? 1 : 8, 8)))
 void eb_pool_kernel(FwdArgs a) {
   const uint32_t blk = a.xcd_remap ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
   const int32_t wid = (int32_t)blk;
@@ -340,11 +335,11 @@ void eb_pool_kernel(FwdArgs a) {
     const int32_t g0 = t * a.batch + b0;
     // the offsets' address needs no table descriptor: issue that load first
     const int64_t my_off = run_offsets(a, g0, nb);
-    const TableMeta m = a.meta[t];
+    const TableMeta m = table_meta(a.meta, t);
     if (m.kind / 8 == DT) {
       const uint32_t queued = a.lq.cap > 0 ? queue_long_bags(a, g0, nb, my_off) : 0u;
       if constexpr (LOG2 >= 0) {
-        pool_all_passes<DT, (1 << (LOG2 >= 0 ? LOG2 : 0)), W>(m, a, g0, nb, b0, my_off, queued);
+        pool_all_passes<DT, (1 << (LOG2 >= 0 ? LOG2 : 0)), W, BIG>(m, a, g0, nb, b0, my_off, queued);
       } else {
         switch (m.kind % 8) {
           EB_LPR(0) EB_LPR(1) EB_LPR(2) EB_LPR(3) EB_LPR(4) EB_LPR(5) EB_LPR(6)
@@ -389,7 +384,7 @@ __device__ __forceinline__ void stage_segment(const FwdArgs &a, int64_t plo, int
 // chunks.  Per 1 KiB column window, the wavefronts' reduced vectors meet in
 // s_part and their sum, in wavefront order, is written to dst (the row's
 // first m.dim values).
-template <int DT, int LPR, bool W>
+template <int DT, int LPR, bool W, bool BIG>
 __device__ __forceinline__ void long_segment(const TableMeta &m, const FwdArgs &a, const int64_t *s_idx,
                                              const float *s_w, int n, float *s_part, float *dst) {
   using R = Reduce<DT, LPR>;
@@ -418,7 +413,7 @@ __device__ __forceinline__ void long_segment(const TableMeta &m, const FwdArgs &
       k.lo = (uint32_t)v;
       k.hi = (uint32_t)(v >> 32);
       k.w = W ? s_w[at] : 0.0f;
-      gather_chunk<DT, LPR, W, SPLIT>(m, a.ctx, resolve(k, m.num_rows, 1), acc, cb, colb, colok);
+      gather_chunk<DT, LPR, W, SPLIT, BIG>(m, a.ctx, resolve(k, m.num_rows, 1), acc, cb, colb, colok);
     }
     if constexpr (SPLIT) {
 #pragma unroll
@@ -444,7 +439,7 @@ __device__ __forceinline__ void long_segment(const TableMeta &m, const FwdArgs &
 }
 
 // The long-bag pass for the lookup's storage type DT (see above).
-template <int DT, bool W>
+template <int DT, bool W, bool BIG>
 __global__ __launch_bounds__(kBlock) void eb_long_pass_kernel(FwdArgs a) {
   constexpr int WIN = kPassBytes / Vals<DT>::esize;
   __shared__ int64_t s_idx[kLongSegMax];
@@ -476,17 +471,17 @@ __global__ __launch_bounds__(kBlock) void eb_long_pass_kernel(FwdArgs a) {
     const int n = (int)((plo + seg < hi ? plo + seg : hi) - plo);
     const int32_t t = (int32_t)(gu / (uint32_t)a.batch);
     const int32_t b = (int32_t)(gu - (uint32_t)t * (uint32_t)a.batch);
-    const TableMeta m = a.meta[t];
+    const TableMeta m = table_meta(a.meta, t);
     stage_segment<W>(a, plo, n, s_idx, s_w);
     float *part = a.lq.part + (size_t)e * a.lq.part_ld;
     switch (m.kind % 8) {
-      case 0: long_segment<DT, 1, W>(m, a, s_idx, s_w, n, s_part, part); break;
-      case 1: long_segment<DT, 2, W>(m, a, s_idx, s_w, n, s_part, part); break;
-      case 2: long_segment<DT, 4, W>(m, a, s_idx, s_w, n, s_part, part); break;
-      case 3: long_segment<DT, 8, W>(m, a, s_idx, s_w, n, s_part, part); break;
-      case 4: long_segment<DT, 16, W>(m, a, s_idx, s_w, n, s_part, part); break;
-      case 5: long_segment<DT, 32, W>(m, a, s_idx, s_w, n, s_part, part); break;
-      case 6: long_segment<DT, 64, W>(m, a, s_idx, s_w, n, s_part, part); break;
+      case 0: long_segment<DT, 1, W, BIG>(m, a, s_idx, s_w, n, s_part, part); break;
+      case 1: long_segment<DT, 2, W, BIG>(m, a, s_idx, s_w, n, s_part, part); break;
+      case 2: long_segment<DT, 4, W, BIG>(m, a, s_idx, s_w, n, s_part, part); break;
+      case 3: long_segment<DT, 8, W, BIG>(m, a, s_idx, s_w, n, s_part, part); break;
+      case 4: long_segment<DT, 16, W, BIG>(m, a, s_idx, s_w, n, s_part, part); break;
+      case 5: long_segment<DT, 32, W, BIG>(m, a, s_idx, s_w, n, s_part, part); break;
+      case 6: long_segment<DT, 64, W, BIG>(m, a, s_idx, s_w, n, s_part, part); break;
       default: break;
     }
     __threadfence();  // this segment's partial row is visible before it is counted
@@ -613,7 +608,7 @@ __device__ __forceinline__ void span_store(const TableMeta &m, const FwdArgs &a,
   }
 
 // One 1 KiB column pass over span w.
-template <int DT, int LOG2, bool W>
+template <int DT, int LOG2, bool W, bool BIG>
 __device__ __forceinline__ void span_walk(const FwdArgs &a, int32_t w, int pass) {
   constexpr int V = Vals<DT>::n;
   constexpr bool SPLIT = EB_INT8_SPLIT_BIAS && DT == kU8 && !W;
@@ -624,11 +619,13 @@ __device__ __forceinline__ void span_walk(const FwdArgs &a, int32_t w, int pass)
 
   int64_t c = p0;
   RawChunk cur = load_chunk<W>(a.indices, a.weights, a.idx64, c, p1);
-  int32_t g0 = search_offsets(a, p0);
+  int32_t g0 = __builtin_amdgcn_readfirstlane(search_offsets(a, p0));
   int64_t off = offset_window(a, g0);
 
   // the bag that holds position pos: its number, first position and end;
-  // false when no bag does (offsets that are no partition)
+  // false when no bag does (offsets that are no partition).  Everything the
+  // walk branches on, and what picks the table, is made wave-uniform: buffer
+  // resources then stay in scalar registers.
   int32_t g = -1;
   int64_t lo = 0, hi = 0;
   auto find = [&](int64_t pos) -> bool {
@@ -638,79 +635,73 @@ __device__ __forceinline__ void span_walk(const FwdArgs &a, int32_t w, int pass)
       off = offset_window(a, g0);
       n = __builtin_popcountll(__ballot(off <= pos));
       if (n == kWave) {
-        g0 = search_offsets(a, pos);
+        g0 = __builtin_amdgcn_readfirstlane(search_offsets(a, pos));
         off = offset_window(a, g0);
         n = __builtin_popcountll(__ballot(off <= pos));
       }
     }
     if (n == 0 || n == kWave || g0 + n - 1 >= a.num_bags) return false;
-    g = g0 + n - 1;
+    g = __builtin_amdgcn_readfirstlane(g0 + n - 1);
     lo = readlane64(off, n - 1);
     hi = readlane64(off, n);
     hi = hi < a.num_indices ? hi : a.num_indices;
-    return lo >= 0 && hi > pos;
+    return __builtin_amdgcn_readfirstlane(lo >= 0 && hi > pos ? 1 : 0) != 0;
   };
 
   float acc[V];
   float cb = 0.0f;
 #pragma unroll
   for (int i = 0; i < V; ++i) acc[i] = 0.0f;
+  uint32_t goes_on = kNoBag;
   bool in_bag = find(c);
-  int32_t t = -1;
-  TableMeta m;
   while (in_bag) {
-    const int32_t tn = g / a.batch;
-    if (tn != t) {
-      t = tn;
-      m = a.meta[t];
-    }
-    const int32_t bag = g;
-    const int64_t blo = lo, bhi = hi;
-    const int64_t e = bhi < p1 ? bhi : p1;
-    cur.n = (int)(e - c < kWave ? e - c : kWave);
-    const bool last = c + kWave >= e;
-    const int64_t cn = last ? e : c + kWave;
-    const bool more = cn < p1;
-    RawChunk nxt;
-    if (more) nxt = load_chunk<W>(a.indices, a.weights, a.idx64, cn, p1);
-    if (last) in_bag = more && find(cn);
-
-    if (m.kind / 8 == DT && pass < m.passes) {
-      const Chunk k = resolve(cur, m.num_rows, a.idx64);
-      const int colb0 = col_base;
-      EB_SPAN_SWITCH((gather_chunk<DT, LPR, W, SPLIT>(m, a.ctx, k, acc, cb, colb0 + (lane % LPR) * 16,
-                                                      colb0 + (lane % LPR) * 16 < m.code_bytes)));
-      if (last) {
-        if constexpr (SPLIT) {
-#pragma unroll
-          for (int i = 0; i < V; ++i) acc[i] += cb;
-          cb = 0.0f;
-        }
-        const bool whole = blo >= p0 && bhi <= p1;
-        float *row = whole ? a.out + (int64_t)(bag - t * a.batch) * a.out_ld + m.out_col
-                           : a.lq.part + ((int64_t)2 * w + (blo >= p0 ? 1 : 0)) * a.lq.part_ld;
-        EB_SPAN_SWITCH((span_store<DT, LPR, W>(m, a, colb0, acc, row, whole && a.mean ? bhi - blo : 0)));
-#pragma unroll
-        for (int i = 0; i < V; ++i) acc[i] = 0.0f;
+    // one bag's part of the span
+    const int32_t t = __builtin_amdgcn_readfirstlane(g / a.batch);
+    const TableMeta m = table_meta(a.meta, t);
+    const int32_t b = g - t * a.batch;
+    const bool started = lo >= p0, whole = started && hi <= p1;
+    goes_on = started && !whole ? (uint32_t)g : kNoBag;
+    const int64_t e = hi < p1 ? hi : p1;
+    const int64_t mean_len = whole && a.mean ? hi - lo : 0;
+    const bool mine = m.kind / 8 == DT && pass < m.passes;
+    while (true) {
+      cur.n = (int)(e - c < kWave ? e - c : kWave);
+      const bool last = c + kWave >= e;
+      c = last ? e : c + kWave;
+      RawChunk nxt;
+      if (c < p1) nxt = load_chunk<W>(a.indices, a.weights, a.idx64, c, p1);
+      if (last) in_bag = c < p1 && find(c);
+      if (mine) {
+        const Chunk k = resolve(cur, m.num_rows, a.idx64);
+        EB_SPAN_SWITCH((gather_chunk<DT, LPR, W, SPLIT, BIG>(m, a.ctx, k, acc, cb, col_base + (lane % LPR) * 16,
+                                                             col_base + (lane % LPR) * 16 < m.code_bytes)));
       }
+      cur = nxt;
+      if (last) break;
     }
-    if (last && !in_bag) {
-      // the span's last bag: does it go on, and did it start here?
-      if (pass == 0 && lane == 0) a.lq.bag[w] = (bhi > p1 && blo >= p0) ? (uint32_t)bag : kNoBag;
-      return;
+    if (mine) {
+      if constexpr (SPLIT) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) acc[i] += cb;
+        cb = 0.0f;
+      }
+      float *row = whole ? a.out + (int64_t)b * a.out_ld + m.out_col
+                         : a.lq.part + ((int64_t)2 * w + (started ? 1 : 0)) * a.lq.part_ld;
+      EB_SPAN_SWITCH((span_store<DT, LPR, W>(m, a, col_base, acc, row, mean_len)));
+#pragma unroll
+      for (int i = 0; i < V; ++i) acc[i] = 0.0f;
     }
-    c = cn;
-    cur = nxt;
   }
-  if (pass == 0 && lane == 0) a.lq.bag[w] = kNoBag;
+  // the span's last bag, if it started here and goes on
+  if (pass == 0 && lane == 0) a.lq.bag[w] = goes_on;
 }
 
-template <int DT, int LOG2, bool W>
+template <int DT, int LOG2, bool W, bool BIG>
 __global__ __launch_bounds__(kWave) void eb_span_kernel(FwdArgs a) {
   const uint32_t blk = a.xcd_remap ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
   const int32_t w = (int32_t)blk;
   if (w >= a.num_spans) return;
-  for (int p = 0; p < a.max_passes; ++p) span_walk<DT, LOG2, W>(a, w, p);
+  for (int p = 0; p < a.max_passes; ++p) span_walk<DT, LOG2, W, BIG>(a, w, p);
 }
 
 #undef EB_SPAN_SWITCH
@@ -860,51 +851,56 @@ __global__ __launch_bounds__(kBlock) void eb_span_fixup_kernel(FwdArgs a) {
 
 typedef void (*KernelFn)(FwdArgs);
 
-// kernel for (storage type, log2 lanes per row or -1, weighted)
-template <int DT, bool W>
+// kernels for (storage type, log2 lanes per row or -1, weighted, big tables)
+template <int DT, bool W, bool BIG>
 KernelFn pick_kernel(int log2) {
   switch (log2) {
-    case 0: return eb_pool_kernel<DT, 0, W>;
-    case 1: return eb_pool_kernel<DT, 1, W>;
-    case 2: return eb_pool_kernel<DT, 2, W>;
-    case 3: return eb_pool_kernel<DT, 3, W>;
-    case 4: return eb_pool_kernel<DT, 4, W>;
-    case 5: return eb_pool_kernel<DT, 5, W>;
-    case 6: return eb_pool_kernel<DT, 6, W>;
-    default: return eb_pool_kernel<DT, -1, W>;
+    case 0: return eb_pool_kernel<DT, 0, W, BIG>;
+    case 1: return eb_pool_kernel<DT, 1, W, BIG>;
+    case 2: return eb_pool_kernel<DT, 2, W, BIG>;
+    case 3: return eb_pool_kernel<DT, 3, W, BIG>;
+    case 4: return eb_pool_kernel<DT, 4, W, BIG>;
+    case 5: return eb_pool_kernel<DT, 5, W, BIG>;
+    case 6: return eb_pool_kernel<DT, 6, W, BIG>;
+    default: return eb_pool_kernel<DT, -1, W, BIG>;
   }
 }
 
-KernelFn pick_kernel(int dt, int log2, bool weighted) {
-  if (dt == kF32) return weighted ? pick_kernel<kF32, true>(log2) : pick_kernel<kF32, false>(log2);
-  if (dt == kF16) return weighted ? pick_kernel<kF16, true>(log2) : pick_kernel<kF16, false>(log2);
-  return weighted ? pick_kernel<kU8, true>(log2) : pick_kernel<kU8, false>(log2);
-}
-
-template <int DT, bool W>
+template <int DT, bool W, bool BIG>
 KernelFn pick_span_kernel(int log2) {
   switch (log2) {
-    case 0: return eb_span_kernel<DT, 0, W>;
-    case 1: return eb_span_kernel<DT, 1, W>;
-    case 2: return eb_span_kernel<DT, 2, W>;
-    case 3: return eb_span_kernel<DT, 3, W>;
-    case 4: return eb_span_kernel<DT, 4, W>;
-    case 5: return eb_span_kernel<DT, 5, W>;
-    case 6: return eb_span_kernel<DT, 6, W>;
-    default: return eb_span_kernel<DT, -1, W>;
+    case 0: return eb_span_kernel<DT, 0, W, BIG>;
+    case 1: return eb_span_kernel<DT, 1, W, BIG>;
+    case 2: return eb_span_kernel<DT, 2, W, BIG>;
+    case 3: return eb_span_kernel<DT, 3, W, BIG>;
+    case 4: return eb_span_kernel<DT, 4, W, BIG>;
+    case 5: return eb_span_kernel<DT, 5, W, BIG>;
+    case 6: return eb_span_kernel<DT, 6, W, BIG>;
+    default: return eb_span_kernel<DT, -1, W, BIG>;
   }
 }
 
-KernelFn pick_span_kernel(int dt, int log2, bool weighted) {
-  if (dt == kF32) return weighted ? pick_span_kernel<kF32, true>(log2) : pick_span_kernel<kF32, false>(log2);
-  if (dt == kF16) return weighted ? pick_span_kernel<kF16, true>(log2) : pick_span_kernel<kF16, false>(log2);
-  return weighted ? pick_span_kernel<kU8, true>(log2) : pick_span_kernel<kU8, false>(log2);
+enum class Kind { kPool, kSpan, kLong };
+
+template <int DT, bool W, bool BIG>
+KernelFn pick_kernel(Kind kind, int log2) {
+  if (kind == Kind::kPool) return pick_kernel<DT, W, BIG>(log2);
+  if (kind == Kind::kSpan) return pick_span_kernel<DT, W, BIG>(log2);
+  return eb_long_pass_kernel<DT, W, BIG>;
 }
 
-KernelFn pick_long_kernel(int dt, bool weighted) {
-  if (dt == kF32) return weighted ? eb_long_pass_kernel<kF32, true> : eb_long_pass_kernel<kF32, false>;
-  if (dt == kF16) return weighted ? eb_long_pass_kernel<kF16, true> : eb_long_pass_kernel<kF16, false>;
-  return weighted ? eb_long_pass_kernel<kU8, true> : eb_long_pass_kernel<kU8, false>;
+template <int DT>
+KernelFn pick_kernel(Kind kind, int log2, bool weighted, bool big) {
+  if (big) return weighted ? pick_kernel<DT, true, true>(kind, log2) : pick_kernel<DT, false, true>(kind, log2);
+  return weighted ? pick_kernel<DT, true, false>(kind, log2) : pick_kernel<DT, false, false>(kind, log2);
+}
+
+KernelFn pick_kernel(Kind kind, const eb_tables *h, int dt, bool weighted) {
+  const int log2 = h->single_log2;
+  const bool big = h->big_tables != 0;
+  if (dt == kF32) return pick_kernel<kF32>(kind, log2, weighted, big);
+  if (dt == kF16) return pick_kernel<kF16>(kind, log2, weighted, big);
+  return pick_kernel<kU8>(kind, log2, weighted, big);
 }
 
 }  // namespace
@@ -958,7 +954,7 @@ static hipError_t launch_spans(const eb_tables *h, FwdArgs &a, const FwdShape &s
   std::lock_guard<std::mutex> lock(*h->enqueue);
   for (int dt = 0; dt < 3 && e == hipSuccess; ++dt) {
     if (!(h->dtype_mask & (1 << dt))) continue;
-    hipLaunchKernelGGL(pick_span_kernel(dt, h->single_log2, sh.weighted), dim3((unsigned)a.num_spans), dim3(kWave), 0,
+    hipLaunchKernelGGL(pick_kernel(Kind::kSpan, h, dt, sh.weighted), dim3((unsigned)a.num_spans), dim3(kWave), 0,
                        h->stream, a);
     e = hipGetLastError();
   }
@@ -1049,11 +1045,11 @@ hipError_t launch_forward(const eb_tables *h, const eb_tensor &indices, const eb
   // followed by the long-bag pass over what it queued
   for (int dt = 0; dt < 3 && e == hipSuccess; ++dt) {
     if (!(h->dtype_mask & (1 << dt))) continue;
-    hipLaunchKernelGGL(pick_kernel(dt, h->single_log2, sh.weighted), dim3((unsigned)num_waves), dim3(kWave), 0,
+    hipLaunchKernelGGL(pick_kernel(Kind::kPool, h, dt, sh.weighted), dim3((unsigned)num_waves), dim3(kWave), 0,
                        h->stream, a);
     e = hipGetLastError();
     if (e == hipSuccess && long_pass) {
-      hipLaunchKernelGGL(pick_long_kernel(dt, sh.weighted), dim3(kLongBlocks), dim3(kBlock), 0, h->stream, a);
+      hipLaunchKernelGGL(pick_kernel(Kind::kLong, h, dt, sh.weighted), dim3(kLongBlocks), dim3(kBlock), 0, h->stream, a);
       e = hipGetLastError();
     }
   }
@@ -1204,8 +1200,12 @@ eb_status eb_create_tables(const eb_table_desc *descs, int32_t num_tables, void 
   h->total_rows = rows_before;
   // the backward sorts (table, row) as one 32-bit key: sum of (rows + 1) must fit
   h->backward_ok = key_before <= (uint64_t)UINT32_MAX;
+  h->big_tables = 0;
   for (int32_t t = 0; t < num_tables; ++t) {
     h->dtype_mask |= 1 << (meta[t].kind / 8);
+    if ((int64_t)meta[t].num_rows * meta[t].row_stride > kMaxBufferBytes ||
+        (meta[t].kind / 8 == kU8 && (int64_t)meta[t].num_rows * meta[t].sb_stride > kMaxBufferBytes))
+      h->big_tables = 1;
     if (meta[t].kind != meta[0].kind) h->single_log2 = -1;
     if (meta[t].dim > h->max_dim) h->max_dim = meta[t].dim;
     if (meta[t].dim != meta[0].dim) h->uniform_dim = 0;
