@@ -100,7 +100,7 @@
  * at the same time, forces how workgroups map onto the GPU's XCDs (default:
  * XCD-contiguous for handles of up to 32 tables, round-robin otherwise).
  * EB_BWD_TILE_CHUNKS=c (1..16) fixes the backward's tiles at 64*c sorted
- * positions (default: 64, or 128 from about two million lookups on), and
+ * positions, one wavefront per 64 (default: 256), and
  * EB_BWD_XCD_REMAP=0|1 its workgroup order (default as for the forward);
  * EB_BWD_SORT_ITEMS=4|8|12|16 fixes the backward sort's blocks at 512
  * threads of that many elements (default: chosen per call from the number of
@@ -322,13 +322,13 @@ typedef enum { EB_OPT_SGD = 0, EB_OPT_ROWWISE_ADAGRAD = 1 } eb_optimizer;
 /*
  * Device workspace (bytes) eb_backward_update needs for num_indices lookups
  * on this handle: 20 bytes per lookup (the sort's two 8-byte element buffers
- * and a bag id), then per tile of 64 or 128 sorted lookups (64*c under
- * EB_BWD_TILE_CHUNKS=c) an 8-byte descriptor and two partial rows of the
- * widest table (8 * max dim bytes), and the sort's counters: 4 bytes per
- * table, pass and digit value, and 8 bytes per pass, digit value and block of
- * 2048 lookups (one more block per table), with digits of up to 9 bits and
- * as many passes as the largest table's row count needs.  Synchronous, host
- * only.
+ * and a bag id), then per 64 or, from about two million lookups on, 128 of
+ * them (64*c under EB_BWD_TILE_CHUNKS=c) an 8-byte descriptor and two partial
+ * rows of the widest table (8 * max dim bytes), which is room for at least a
+ * call's tiles, and the sort's counters: 4 bytes per table, pass and digit
+ * value, and 8 bytes per pass, digit value and block of 2048 lookups (one more
+ * block per table), with digits of up to 9 bits and as many passes as the
+ * largest table's row count needs.  Synchronous, host only.
  */
 eb_status eb_backward_workspace_size(const eb_tables *tables, int64_t num_indices, size_t *bytes);
 

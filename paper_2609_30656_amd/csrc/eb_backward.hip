@@ -20,11 +20,11 @@
 //      first, one stable pass per digit: each row's occurrences become one
 //      run, in position order, and each table's positions stay inside that
 //      table's range of the sorted array;
-//   3. each table's sorted range is cut into tiles of 64 or 128 positions; a
-//      wavefront walks its tile's runs, pools each run's gradient rows with the
-//      forward's 16-byte-slice gather and reduce-scatter (the gradient is an
-//      fp32 "table" of B rows), and updates the run's table row; a run that
-//      crosses a tile boundary leaves a partial sum in a per-tile slot;
+//   3. each table's sorted range is cut into tiles of 256 positions; a
+//      workgroup's lane groups walk equal parts of a tile, add the gradient
+//      rows of each run (the gradient is an fp32 "table" of B rows), put the
+//      runs that cross groups together, and update each run's table row; a run
+//      that crosses a tile boundary leaves a partial sum in a per-tile slot;
 //   4. a fix-up pass sums each crossing run's partials in a fixed order (set
 //      by the run's length) and updates its row; each tile's info word (its
 //      table, the key of its last run, whether that run goes on and whether
@@ -36,6 +36,7 @@
 
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "eb_device.h"
 
@@ -109,6 +110,18 @@ struct BwdArgs {
 
 __device__ __forceinline__ int64_t load_offset(const BwdArgs &a, int64_t g) {
   return a.idx64 ? static_cast<const int64_t *>(a.offsets)[g] : (int64_t) static_cast<const int32_t *>(a.offsets)[g];
+}
+
+// offsets[g + 1] - offsets[g], in one access
+__device__ __forceinline__ int64_t bag_length(const BwdArgs &a, int64_t g) {
+  typedef int64_t i64x2 __attribute__((ext_vector_type(2), aligned(8)));
+  typedef int32_t i32x2 __attribute__((ext_vector_type(2), aligned(4)));
+  if (a.idx64) {
+    const i64x2 o = *(const EB_GLOBAL i64x2 *)(static_cast<const int64_t *>(a.offsets) + g);
+    return o[1] - o[0];
+  }
+  const i32x2 o = *(const EB_GLOBAL i32x2 *)(static_cast<const int32_t *>(a.offsets) + g);
+  return (int64_t)o[1] - o[0];
 }
 
 __device__ __forceinline__ int64_t clamp_pos(int64_t p, int64_t lo, int64_t hi) {
@@ -583,15 +596,20 @@ void eb_bwd_sort_pass_kernel(BwdArgs a, int32_t pass) {
 }
 
 // table owning tile w: the last table whose first tile is <= w (empty tables
-// own no tile and are skipped)
+// own no tile and are skipped), 64 tables per step
 __device__ __forceinline__ int32_t table_of_tile(const BwdArgs &a, int32_t w) {
-  int32_t lo = 0, hi = a.num_tables - 1;
-  while (lo < hi) {
-    const int32_t mid = (lo + hi + 1) / 2;
-    if (a.tile_start[mid] <= w) lo = mid;
-    else hi = mid - 1;
+  const int lane = threadIdx.x & (kWave - 1);
+  int32_t lo = 0, range = a.num_tables;
+  while (range > 0) {
+    const int32_t step = (range + kWave - 1) / kWave;
+    const int32_t t = lo + lane * step;
+    const bool in = t < a.num_tables;
+    const int c = __builtin_popcountll(__ballot(in && a.tile_start[in ? t : 0] <= w));
+    lo += (c > 0 ? c - 1 : 0) * step;
+    if (step == 1) break;
+    range = step;
   }
-  return lo;
+  return __builtin_amdgcn_readfirstlane(lo);
 }
 
 // Sum of x over the 64 lanes (fixed butterfly order).
@@ -610,6 +628,7 @@ typedef EB_GLOBAL unsigned char growb;
 typedef EB_GLOBAL float gf32;
 typedef EB_GLOBAL _Float16 gf16;
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
@@ -621,92 +640,59 @@ __device__ __forceinline__ gf32 *state_of(const BwdArgs &a, const TableMeta &m, 
   return (gf32 *)a.state + m.state_base + row;
 }
 
-// K = 1, 2 or 4 consecutive values of a row of type TDT from column col (a
-// multiple of K, so the access is aligned to its size), in one access.
-template <int TDT, int K>
-__device__ __forceinline__ void load_vals(growb *base, int col, float (&w)[K]) {
-  static_assert(K == 1 || K == 2 || K == 4, "one access holds 1, 2 or 4 values");
+// Four consecutive values of a row of type TDT from column col (a multiple of
+// 4, so the access is aligned to its size), in one access.
+template <int TDT>
+__device__ __forceinline__ void load_vals(growb *base, int col, float (&w)[4]) {
   if constexpr (TDT == kF32) {
-    gf32 *p = (gf32 *)base + col;
-    if constexpr (K == 4) {
-      const f32x4 v = *(EB_GLOBAL f32x4 *)p;
+    const f32x4 v = *(EB_GLOBAL f32x4 *)((gf32 *)base + col);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) w[i] = v[i];
-    } else if constexpr (K == 2) {
-      const f32x2 v = *(EB_GLOBAL f32x2 *)p;
-      w[0] = v[0];
-      w[1] = v[1];
-    } else {
-      w[0] = *p;
-    }
+    for (int i = 0; i < 4; ++i) w[i] = v[i];
   } else {
-    gf16 *p = (gf16 *)base + col;
-    if constexpr (K == 4) {
-      const f16x4 v = *(EB_GLOBAL f16x4 *)p;
+    const f16x4 v = *(EB_GLOBAL f16x4 *)((gf16 *)base + col);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) w[i] = (float)v[i];
-    } else if constexpr (K == 2) {
-      const f16x2 v = *(EB_GLOBAL f16x2 *)p;
-      w[0] = (float)v[0];
-      w[1] = (float)v[1];
-    } else {
-      w[0] = (float)*p;
-    }
+    for (int i = 0; i < 4; ++i) w[i] = (float)v[i];
   }
 }
 
 // The store matching load_vals (fp16 rows round to nearest).
-template <int TDT, int K>
-__device__ __forceinline__ void store_vals(growb *base, int col, const float (&w)[K]) {
-  static_assert(K == 1 || K == 2 || K == 4, "one access holds 1, 2 or 4 values");
-  if constexpr (TDT == kF32) {
-    gf32 *p = (gf32 *)base + col;
-    if constexpr (K == 4) *(EB_GLOBAL f32x4 *)p = f32x4{w[0], w[1], w[2], w[3]};
-    else if constexpr (K == 2) *(EB_GLOBAL f32x2 *)p = f32x2{w[0], w[1]};
-    else *p = w[0];
-  } else {
-    gf16 *p = (gf16 *)base + col;
-    if constexpr (K == 4) {
-      *(EB_GLOBAL f16x4 *)p = f16x4{(_Float16)w[0], (_Float16)w[1], (_Float16)w[2], (_Float16)w[3]};
-    } else if constexpr (K == 2) {
-      *(EB_GLOBAL f16x2 *)p = f16x2{(_Float16)w[0], (_Float16)w[1]};
-    } else {
-      *p = (_Float16)w[0];
-    }
-  }
+template <int TDT>
+__device__ __forceinline__ void store_vals(growb *base, int col, const float (&w)[4]) {
+  if constexpr (TDT == kF32) *(EB_GLOBAL f32x4 *)((gf32 *)base + col) = f32x4{w[0], w[1], w[2], w[3]};
+  else
+    *(EB_GLOBAL f16x4 *)((gf16 *)base + col) = f16x4{(_Float16)w[0], (_Float16)w[1], (_Float16)w[2], (_Float16)w[3]};
 }
 
-// The values a row update reads, loaded ahead of the gather that produces
-// the row's gradient: the lane's K table values and the Adagrad state.
-template <int TDT, int K>
+// The values a row update of the fix-up reads, loaded ahead of the sum that
+// produces the row's gradient: the lane's four table values and the Adagrad
+// state.
 struct RowPrefetch {
-  float w[K];
+  float w[4];
   float s;
 };
 
-template <int TDT, int K>
-__device__ __forceinline__ RowPrefetch<TDT, K> prefetch_row(const TableMeta &m, const BwdArgs &a, int64_t row, bool own,
-                                                           int col) {
-  RowPrefetch<TDT, K> p;
+template <int TDT>
+__device__ __forceinline__ RowPrefetch prefetch_row(const TableMeta &m, const BwdArgs &a, int64_t row, bool own, int col) {
+  RowPrefetch p;
   p.s = a.opt == kOptRowwiseAdagrad ? *state_of(a, m, row) : 0.0f;
 #pragma unroll
-  for (int i = 0; i < K; ++i) p.w[i] = 0.0f;
-  if (own) load_vals<TDT, K>(row_bytes(m, row), col, p.w);
+  for (int i = 0; i < 4; ++i) p.w[i] = 0.0f;
+  if (own) load_vals<TDT>(row_bytes(m, row), col, p.w);
   return p;
 }
 
-// Optimizer step on row `row` of table m.  Lane holds K gradient values for
-// columns [col, col + K) when `own`; the columns of all owning lanes cover
-// the row exactly once.  `p` holds the row's values read beforehand.
-template <int TDT, int K>
-__device__ __forceinline__ void apply_update(const TableMeta &m, const BwdArgs &a, int64_t row, const float (&g)[K],
-                                             bool own, int col, const RowPrefetch<TDT, K> &p) {
+// Optimizer step on row `row` of table m.  Lane holds four gradient values
+// from column col on when `own`; the columns of all owning lanes cover the row
+// exactly once.  `p` holds the row's values read beforehand.
+template <int TDT>
+__device__ __forceinline__ void apply_update(const TableMeta &m, const BwdArgs &a, int64_t row, const float (&g)[4],
+                                             bool own, int col, const RowPrefetch &p) {
   float scale = a.lr;
   if (a.opt == kOptRowwiseAdagrad) {
     float sq = 0.0f;
     if (own) {
 #pragma unroll
-      for (int i = 0; i < K; ++i) sq = fmaf(g[i], g[i], sq);
+      for (int i = 0; i < 4; ++i) sq = fmaf(g[i], g[i], sq);
     }
     sq = wave_sum(sq);
     const float s_new = p.s + sq / (float)m.dim;
@@ -714,302 +700,490 @@ __device__ __forceinline__ void apply_update(const TableMeta &m, const BwdArgs &
     if ((threadIdx.x & (kWave - 1)) == 0) *state_of(a, m, row) = s_new;
   }
   if (own) {
-    float nw[K];
+    float nw[4];
 #pragma unroll
-    for (int i = 0; i < K; ++i) nw[i] = fmaf(-scale, g[i], p.w[i]);
-    store_vals<TDT, K>(row_bytes(m, row), col, nw);
+    for (int i = 0; i < 4; ++i) nw[i] = fmaf(-scale, g[i], p.w[i]);
+    store_vals<TDT>(row_bytes(m, row), col, nw);
   }
 }
 
-// Complete runs inside one chunk, several at once: the runs that start at
-// heads h_0 < ... < h_nruns of the chunk (run k is [h_k, h_k+1)) go to lane
-// groups of LPRS lanes, one run per group, G = 64 / LPRS runs per round.  A
-// group walks its run's entries in order (P 16-byte loads per lane per
-// gradient row), then applies the optimizer step to the run's row itself:
-// no cross-group reduction, and one memory round trip per round of G runs.
-// A gradient row of 16 or more 16-byte slices is held by half as many lanes,
-// two slices each: twice the runs per round, for the same registers that the
-// widest row already takes.
-template <int TDT, int LPR_NAT>
-__device__ __forceinline__ void short_runs(const BwdArgs &a, const TableMeta &m, const TableMeta &gm, const Chunk &ch,
-                                           uint32_t key, uint64_t hs, int nruns, int *starts) {
-  constexpr int LPRS = LPR_NAT >= 16 ? LPR_NAT / 2 : LPR_NAT;
-  constexpr int P = LPR_NAT / LPRS;
-  constexpr int G = kWave / LPRS;
-  constexpr int US = P >= 2 ? 2 : 4;
-  constexpr int NV = 4 * P;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int grp = lane / LPRS, sub = lane % LPRS;
-  const uint32_t kmin = m.key_base, sentinel = m.key_base + (uint32_t)m.num_rows;
-  // position of the head of each rank (rank = heads below it)
-  if ((hs >> lane) & 1ull) starts[__builtin_popcountll(hs & ((1ull << lane) - 1ull))] = lane;
-  __builtin_amdgcn_wave_barrier();
-  const int colb0 = sub * 16 * P;
-  for (int r0 = 0; r0 < nruns; r0 += G) {
-    const int k = r0 + grp;
-    const bool active = k < nruns;
-    const int st = active ? starts[k] : 0;
-    const int len = active ? starts[k + 1] - st : 0;
-    const uint32_t rkey = (uint32_t)__shfl((int)key, st & (kWave - 1));
-    const bool valid = active && rkey >= kmin && rkey < sentinel;
-    const int64_t row = valid ? (int64_t)(rkey - kmin) : 0;
-    int maxlen = len;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) maxlen = max(maxlen, __shfl_xor(maxlen, o));
-    // the row's values and state, read before the gradient gather
-    float wv[NV];
-    float s_old = 0.0f;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) wv[i] = 0.0f;
-    const int col0 = colb0 / 4;
-    if (valid) {
-      if (a.opt == kOptRowwiseAdagrad) s_old = *state_of(a, m, row);
-      growb *base = row_bytes(m, row);
-#pragma unroll
-      for (int pp = 0; pp < P; ++pp) {
-        // dim is a multiple of 4: four columns are all in the row or all past it
-        if (col0 + 4 * pp < m.dim) {
-          float t4[4];
-          load_vals<TDT, 4>(base, col0 + 4 * pp, t4);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) wv[4 * pp + i] = t4[i];
-        }
-      }
-    }
-    float acc[NV];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) acc[i] = 0.0f;
-    for (int u = 0; u < maxlen; u += US) {
-      u32x4 v[US][P];
-      float c[US];
-#pragma unroll
-      for (int q = 0; q < US; ++q) {
-        const int e = st + u + q;
-        const uint32_t b = (uint32_t)__shfl((int)ch.row, e & (kWave - 1));
-        c[q] = __shfl(ch.w, e & (kWave - 1));
-        const bool ok = valid && (u + q < len) && b != kBadRow;
-        gbyte *pr = ok ? (gbyte *)gm.data + (uint64_t)b * gm.row_stride : (gbyte *)a.ctx.zero;
-#pragma unroll
-        for (int pp = 0; pp < P; ++pp) {
-          const int cb = colb0 + 16 * pp;
-          v[q][pp] = load_slice<kF32>((cb < gm.code_bytes ? pr : (gbyte *)a.ctx.zero) + cb);
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < US; ++q) {
-#pragma unroll
-        for (int pp = 0; pp < P; ++pp) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) acc[4 * pp + i] = fmaf(c[q], __uint_as_float(v[q][pp][i]), acc[4 * pp + i]);
-        }
-      }
-    }
-    float scale = a.lr;
-    if (a.opt == kOptRowwiseAdagrad) {
-      float sq = 0.0f;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) sq = fmaf(acc[i], acc[i], sq);  // zero past the row's end
-#pragma unroll
-      for (int o = 1; o < LPRS; o <<= 1) sq += __shfl_xor(sq, o);
-      const float s_new = s_old + sq / (float)m.dim;
-      scale = a.lr / (sqrtf(s_new) + a.eps);
-      if (valid && sub == 0) *state_of(a, m, row) = s_new;
-    }
-    if (valid) {
-      growb *base = row_bytes(m, row);
-#pragma unroll
-      for (int pp = 0; pp < P; ++pp) {
-        if (col0 + 4 * pp < m.dim) {
-          float t4[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) t4[i] = fmaf(-scale, acc[4 * pp + i], wv[4 * pp + i]);
-          store_vals<TDT, 4>(base, col0 + 4 * pp, t4);
-        }
-      }
-    }
+// Sum of x over each group of LG consecutive lanes, on all of them (fixed
+// order): DPP within 16 lanes, a row swap for 32.
+template <int LG>
+__device__ __forceinline__ float group_sum(float x) {
+  auto dpp = [](float v, auto ctrl) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value,
+                                                                 0xf, 0xf, false));
+  };
+  if constexpr (LG >= 2) x += dpp(x, std::integral_constant<int, 0xB1>{});   // lanes 1 0 3 2
+  if constexpr (LG >= 4) x += dpp(x, std::integral_constant<int, 0x4E>{});   // lanes 2 3 0 1
+  if constexpr (LG >= 8) x += dpp(x, std::integral_constant<int, 0x141>{});  // mirrored half rows
+  if constexpr (LG >= 16) x += dpp(x, std::integral_constant<int, 0x140>{});  // mirrored rows
+  if constexpr (LG >= 32) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
   }
-  __builtin_amdgcn_wave_barrier();
+  return x;
 }
 
-// Step 3b: pool the runs of one tile and update their rows (or leave
-// partials).  LPR lanes hold one fp32 gradient row of 4*dim bytes.
-template <int TDT, int LPR>
+// Step 3b: the tiles.  A tile is 64 sorted positions per wavefront of a
+// workgroup.  In a wavefront a gradient row is held by a group of LG lanes (P
+// 16-byte slices each, LG * P * 4 values), and each of the 64 / LG groups
+// walks LG consecutive positions, whatever runs they belong to: every
+// wavefront does the same 64 gradient rows in the same number of round trips,
+// so none is slow.  (With a run per group instead, a chunk of rows that occur
+// once took sixteen rounds where a piece of a hot run took one or two, tile
+// times spread from a few to 111 us, and the launch drained for a fifth of its
+// time.  The kernel took 262 us on 8 fp16 tables of 128 values at batch 16 384,
+// mean pooling, now 208; 74 and 58 on 26 fp32 tables of 64 at batch 2048; 586
+// and 465 on 48 mixed fp16 tables at batch 8192.)  What bounds it now is random
+// access to memory: 0.7 GB in the first of these, a third of it writes and
+// 4-byte optimizer states, at 3.3 TB/s.
+//   * A run that starts and ends inside a group is finished there: its table
+//     row and state are read with its last gradient rows, and updated.
+//   * The other runs are put together from their groups' partial sums: the
+//     head (a run that entered from the group before and ends here) and the
+//     tail (the run that goes on past the group).  A segmented scan over the
+//     wavefront's groups, then over the workgroup's wavefronts through LDS,
+//     adds the tails; the group in which a run ends updates its row.
+//   * A run that enters the tile or leaves it leaves its sum in the tile's
+//     carry slots, for the fix-up.
+// The order of every sum is fixed by the sorted positions.
+
+// Positions of a group walked per round trip: four where the registers allow
+// it (fp32 rows of two slices take two: four would spill).
+template <int TDT, int P, int LG>
+struct TileBatch {
+  static constexpr int most = P == 1 || TDT == kF16 ? 4 : 2;
+  static constexpr int q = LG < most ? LG : most;
+};
+
+// Wavefronts (64-position chunks) per tile.  More leave fewer partial rows to
+// the fix-up, fewer wait less for each other at the tile's barrier; 26 fp32
+// tables of 64 at batch 2048, 8 fp16 tables of 128 at batch 16 384 and 48
+// mixed fp16 tables at batch 8192 took, per step, 138/420/905 us with one,
+// 113/334/695 with two, 112/323/680 with four and 120/340/714 with eight.
+constexpr int kTileWaves = 4;
+constexpr int kMaxTileWaves = 16;  // EB_BWD_TILE_CHUNKS
+
+// A table's rows and optimizer state as the tiles read and write them: a
+// lane's four columns of a row at a time.  Rows are touched once per step, so
+// they pass L2 by (non-temporal), which keeps it for the gradient rows.
+// Without BIG through buffer resources: an access to a row that does not
+// exist (kNoOffset), or past the row's columns (column byte kNoOffset; the
+// sums saturate), reads zero and writes nothing.
+//
+// A lane of an fp16 row with two slices holds eight columns next to each
+// other, one 16-byte access; other rows are accessed slice by slice (4 columns:
+// 16 bytes fp32, 8 bytes fp16).
+template <int TDT, int P>
+struct RowSlice {
+  static constexpr int cols = TDT == kF16 && P == 2 ? 8 : 4;
+  static constexpr int count = 4 * P / cols;
+  static constexpr int bytes = cols * (TDT == kF32 ? 4 : 2);
+  typedef float f32xN __attribute__((ext_vector_type(cols)));
+  typedef _Float16 f16xN __attribute__((ext_vector_type(cols)));
+  typedef typename std::conditional<TDT == kF32, f32xN, f16xN>::type type;
+};
+constexpr int kNonTemporal = 2;  // cache policy of the buffer operations
+
+template <int TDT, int P, bool BIG>
+struct TableRows;
+template <int TDT, int P>
+struct TableRows<TDT, P, false> {
+  typedef uint32_t addr;
+  typedef typename RowSlice<TDT, P>::type slice;
+  static constexpr int bytes = RowSlice<TDT, P>::bytes;
+  __amdgpu_buffer_rsrc_t rows, state;
+  uint32_t stride;
+  __device__ __forceinline__ TableRows(const BwdArgs &a, const TableMeta &m) : stride(m.row_stride) {
+    rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(m.data), 0, (int)((uint32_t)m.num_rows * m.row_stride),
+                                             kBufferFlags);
+    state = __builtin_amdgcn_make_buffer_rsrc(a.state + m.state_base, 0, (int)((uint32_t)m.num_rows * 4u), kBufferFlags);
+  }
+  __device__ __forceinline__ addr row_at(bool on, uint32_t row) const { return on ? row * stride : kNoOffset; }
+  __device__ __forceinline__ addr state_at(bool on, uint32_t row) const { return on ? row * 4u : kNoOffset; }
+  __device__ __forceinline__ slice load(addr at, uint32_t colb) const {
+    const uint32_t o = __builtin_elementwise_add_sat(at, colb);
+    if constexpr (bytes == 16) return __builtin_bit_cast(slice, __builtin_amdgcn_raw_buffer_load_b128(rows, o, 0, kNonTemporal));
+    else return __builtin_bit_cast(slice, __builtin_amdgcn_raw_buffer_load_b64(rows, o, 0, kNonTemporal));
+  }
+  __device__ __forceinline__ void store(addr at, uint32_t colb, slice v) const {
+    const uint32_t o = __builtin_elementwise_add_sat(at, colb);
+    if constexpr (bytes == 16) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rows, o, 0, kNonTemporal);
+    else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rows, o, 0, kNonTemporal);
+  }
+  __device__ __forceinline__ float load_state(addr at) const {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(state, at, 0, kNonTemporal));
+  }
+  __device__ __forceinline__ void store_state(addr at, float v) const {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), state, at, 0, kNonTemporal);
+  }
+};
+template <int TDT, int P>
+struct TableRows<TDT, P, true> {
+  typedef uint64_t addr;  // 0: no row
+  typedef typename RowSlice<TDT, P>::type slice;
+  const unsigned char *rows, *zero;
+  float *state;
+  uint32_t stride;
+  __device__ __forceinline__ TableRows(const BwdArgs &a, const TableMeta &m)
+      : rows(m.data), zero(a.ctx.zero), state(a.state + m.state_base), stride(m.row_stride) {}
+  __device__ __forceinline__ addr row_at(bool on, uint32_t row) const {
+    return on ? reinterpret_cast<uint64_t>(rows) + (uint64_t)row * stride : 0u;
+  }
+  __device__ __forceinline__ addr state_at(bool on, uint32_t row) const {
+    return on ? reinterpret_cast<uint64_t>(state) + (uint64_t)row * 4u : 0u;
+  }
+  __device__ __forceinline__ slice load(addr at, uint32_t colb) const {
+    const bool ok = at != 0 && colb != kNoOffset;
+    return *(const EB_GLOBAL slice *)(ok ? at + colb : reinterpret_cast<uint64_t>(zero));
+  }
+  __device__ __forceinline__ void store(addr at, uint32_t colb, slice v) const {
+    if (at != 0 && colb != kNoOffset) *(EB_GLOBAL slice *)(at + colb) = v;
+  }
+  __device__ __forceinline__ float load_state(addr at) const {
+    return *(const EB_GLOBAL float *)(at != 0 ? at : reinterpret_cast<uint64_t>(zero));
+  }
+  __device__ __forceinline__ void store_state(addr at, float v) const {
+    if (at != 0) *(EB_GLOBAL float *)at = v;
+  }
+};
+
+// 16 bytes of a gradient row from column byte colb (kNoOffset: zeros)
+__device__ __forceinline__ u32x4 load_grad(const RowSource<kF32, false> &g, uint32_t at, uint32_t colb) {
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(g.rows, __builtin_elementwise_add_sat(at, colb), 0, 0));
+}
+__device__ __forceinline__ u32x4 load_grad(const RowSource<kF32, true> &g, uint64_t at, uint32_t colb) {
+  return load_slice<kF32>((gbyte *)(colb != kNoOffset ? at + colb : reinterpret_cast<uint64_t>(g.zero)));
+}
+
+template <int TDT, int LPR, bool BIG>
 __device__ __forceinline__ void tile_body(const BwdArgs &a, const TableMeta &m, int32_t t, int32_t w, int32_t k,
-                                          int *starts) {
-  using R = Reduce<kF32, LPR>;
-  constexpr int KEEP = R::KEEP;
+                                          float *s_sum, uint32_t *s_flag) {
+  constexpr int LG = LPR >= 32 ? LPR / 2 : LPR;
+  constexpr int P = LPR / LG;
+  constexpr int G = kWave / LG;
+  constexpr int NV = 4 * P;
+  constexpr int Q = TileBatch<TDT, P, LG>::q;
   const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int waves = a.tile_size / kWave;
+  const int grp = lane / LG, sub = lane % LG, f = grp * LG;
   int64_t p0, p1;
   table_range(a, t, p0, p1);
   const int64_t s = p0 + (int64_t)k * a.tile_size;
   const int64_t e = s + a.tile_size < p1 ? s + a.tile_size : p1;
-  if (s >= e) return;
-  const uint32_t before = s > p0 ? a.skeys[s - 1] : kNoKey;
-  const uint32_t after = e < p1 ? a.skeys[e] : kNoKey;
-  const uint32_t key_last = a.skeys[e - 1];
+  if (s >= e) return;  // (the whole workgroup)
   const uint32_t kmin = m.key_base, sentinel = m.key_base + (uint32_t)m.num_rows;
-  if (lane == 0) {
+
+  // this lane's position: its key, its neighbours', its gradient row
+  const int64_t pos = s + wave * kWave + lane;
+  const bool in = pos < e;
+  const int64_t pc = in ? pos : s;
+  const uint32_t key0 = a.skeys[pc];
+  const uint32_t sv = a.spos[pc];
+  const uint32_t prev = pc > p0 ? a.skeys[pc - 1] : kNoKey;
+  const uint32_t next = pc + 1 < p1 ? a.skeys[pc + 1] : kNoKey;
+  if (threadIdx.x == 0) {
+    const uint32_t key_last = a.skeys[e - 1];
+    const uint32_t after = e < p1 ? a.skeys[e] : kNoKey;
     const bool cont = after != kNoKey && after == key_last;
-    const bool owns = cont && key_last != before && key_last < sentinel && key_last >= kmin;
+    const bool owns = cont && key_last != prev && key_last < sentinel && key_last >= kmin;
     a.tile_info[w] = (uint64_t)((cont ? kTileContinues : 0) | (owns ? kTileOwnsRun : 0)) | ((uint64_t)t << 8) |
                      ((uint64_t)key_last << 32);
   }
-
+  const bool row_ok = in && key0 >= kmin && key0 < sentinel;
+  uint32_t brow = kBadRow;  // the position's example
+  float coef = 0.0f;
+  if (row_ok) {
+    const int32_t g = a.sorted_bags ? (int32_t)sv : a.bag_of[sv];
+    const int64_t b = (int64_t)g - (int64_t)t * a.batch;
+    if (b >= 0 && b < a.batch) {
+      brow = (uint32_t)b;
+      coef = 1.0f;
+      if (a.coef == 1) {
+        coef = a.weights[sv];
+      } else if (a.coef == 2) {
+        const int64_t L = bag_length(a, g);
+        coef = L > 0 ? 1.0f / (float)L : 0.0f;
+      }
+    }
+  }
   // the gradient rows of this table as an fp32 table of B rows
   TableMeta gm = m;
   gm.data = reinterpret_cast<const unsigned char *>(a.grad + m.out_col);
   gm.row_stride = (uint32_t)(a.grad_ld * 4);
   gm.num_rows = a.batch;
-  gm.code_bytes = 4 * m.dim;
-  const int colb = (lane % LPR) * 16;
-  const bool colok = colb < gm.code_bytes;
-  const int col = colb / 4 + R::first_value(lane);
-  const bool own = R::stores(lane) && colok;
+  const RowSource<kF32, BIG> grads(gm, a.ctx);
+  const RowAddr<BIG> at = grads.locate(brow);
 
-  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  bool first_run = true;
-  // Values of the row the current run will update, read when the run starts
-  // (a run that crossed into this tile, or goes on past it, updates nothing
-  // here); no other wavefront writes that row during this launch.
-  RowPrefetch<TDT, KEEP> pre;
-  auto start_run = [&](uint32_t rkey) {
-    const bool valid = rkey >= kmin && rkey < sentinel;
-    if (valid && !(first_run && rkey == before) && rkey != after)
-      pre = prefetch_row<TDT, KEEP>(m, a, (int64_t)(rkey - kmin), own, col);
-  };
-  // Finish the run with key rkey whose terms are all in acc: update its row,
-  // or leave a partial when it crosses a tile boundary.
-  auto finish = [&](uint32_t rkey, bool reaches_end) {
-    const bool valid = rkey >= kmin && rkey < sentinel;
-    const bool started_before = first_run && rkey == before;
-    const bool continues_after = reaches_end && rkey == after;
-    if (valid) {
-      R::run(acc);
-      float gk[KEEP];
+  // runs: where they start and end, by position and by group
+  const bool start = in && key0 != prev, end = in && key0 != next;
+  const uint64_t starts = __ballot(start);
+  const uint32_t gmask = LG == 64 ? ~0u : (uint32_t)((1ull << (LG < 64 ? LG : 0)) - 1ull);
+  const uint32_t gstarts = (uint32_t)(starts >> f) & gmask;  // of this group (bit: position)
+  const bool here = (gstarts & (uint32_t)((2ull << sub) - 1ull)) != 0;  // the position's run started in the group
+  const uint64_t upd = __ballot(end && here && row_ok), hends = __ballot(end && !here);
+  const uint32_t gupd = (uint32_t)(upd >> f) & gmask, ghead = (uint32_t)(hends >> f) & gmask;
+  const uint32_t gends = (uint32_t)(__ballot(end) >> f) & gmask;
+  const bool tail = s + wave * kWave + f + LG - 1 < e && !((gends >> (LG - 1)) & 1u);
+  const uint32_t row0 = row_ok ? key0 - kmin : 0u;
+
+  // the lane's columns: gradient slice j holds columns col(j) .. col(j) + 3
+  typedef RowSlice<TDT, P> Slice;
+  constexpr int S = Slice::count, C = Slice::cols;
+  auto col = [&](int j) { return C == 8 ? 4 * (2 * sub + j) : 4 * (sub + LG * j); };
+  bool cok[P];
+  uint32_t colb[P], tcolb[S];  // their bytes in a gradient row and in a table row
 #pragma unroll
-      for (int i = 0; i < KEEP; ++i) gk[i] = acc[i];
-      if (!started_before && !continues_after) {
-        apply_update<TDT, KEEP>(m, a, (int64_t)(rkey - kmin), gk, own, col, pre);
-      } else if (own) {
-        gf32 *slot = (gf32 *)a.carry + ((int64_t)2 * w + (started_before ? 0 : 1)) * a.max_dim;
-        store_vals<kF32, KEEP>((growb *)slot, col, gk);
+  for (int j = 0; j < P; ++j) {
+    cok[j] = col(j) < m.dim;
+    colb[j] = cok[j] ? 4 * col(j) : kNoOffset;
+  }
+#pragma unroll
+  for (int j = 0; j < S; ++j) tcolb[j] = cok[j] ? Slice::bytes * (sub + LG * j) : kNoOffset;
+  typedef TableRows<TDT, P, BIG> Rows;
+  typedef typename Rows::addr addr_t;
+  typedef typename Rows::slice slice_t;
+  const Rows table(a, m);
+  const bool adagrad = a.opt == kOptRowwiseAdagrad;
+  // 1 / dim is exact for a power of two, so the product rounds as the quotient does
+  const bool pow2 = (m.dim & (m.dim - 1)) == 0;
+  const float fdim = (float)m.dim, rdim = 1.0f / fdim;
+  auto square = [&](const float (&g)[NV]) {  // sum of g^2 over the row (columns past it hold zeros)
+    float sq = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) sq = fmaf(g[i], g[i], sq);
+    return group_sum<LG>(sq);
+  };
+  auto step_size = [&](float sq, float s_old, float &s_new) {
+    s_new = s_old + (pow2 ? sq * rdim : sq / fdim);
+    return a.lr / (sqrtf(s_new) + a.eps);
+  };
+  auto update = [&](addr_t row, const float (&g)[NV], const slice_t (&old)[S], float scale) {
+#pragma unroll
+    for (int j = 0; j < S; ++j) {
+      slice_t nw;
+#pragma unroll
+      for (int i = 0; i < C; ++i) nw[i] = fmaf(-scale, g[C * j + i], (float)old[j][i]);
+      table.store(row, tcolb[j], nw);
+    }
+  };
+
+  // the walk, Q positions of every group per round trip.  What each row needs
+  // once (its state, the square root and quotients of its step) is done by one
+  // lane per position of the batch, for all of them together.
+  const bool mine = ((gupd >> sub) & 1u) != 0;  // this lane's position ends a run of its group
+  const addr_t urow = table.row_at(mine, row0), ustate = table.state_at(mine, row0);
+  float acc[NV], head[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) acc[i] = head[i] = 0.0f;
+  constexpr uint64_t every_group = G == 64 ? ~0ull : ~0ull / ((1ull << (G == 64 ? 1 : LG)) - 1ull);
+#pragma unroll 1
+  for (int q0 = 0; q0 < LG; q0 += Q) {
+    if (s + wave * kWave + q0 >= e) break;
+    const uint64_t batch = (every_group * ((1ull << Q) - 1ull)) << q0;  // the batch's positions in every group
+    const bool updates = (upd & batch) != 0;
+    decltype(at.row) ar[Q];
+    float c[Q];
+#pragma unroll
+    for (int u = 0; u < Q; ++u) {
+      ar[u] = from_lane(at.row, f + q0 + u);
+      c[u] = __shfl(coef, f + q0 + u);
+    }
+    addr_t ur[Q], us = 0;
+    slice_t old[Q][S];
+    float s_old = 0.0f;
+    if (updates) {
+#pragma unroll
+      for (int u = 0; u < Q; ++u) {
+        ur[u] = from_lane(urow, f + q0 + u);
+#pragma unroll
+        for (int j = 0; j < S; ++j) old[u][j] = table.load(ur[u], tcolb[j]);
+      }
+      if (adagrad) {
+        const bool on = sub < Q;
+        us = from_lane(ustate, f + q0 + (on ? sub : 0));
+        us = on ? us : table.state_at(false, 0);
+        s_old = table.load_state(us);
       }
     }
-    first_run = false;
+    float v[Q][NV];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] = 0.0f;
-  };
-  bool pending = false;  // acc holds a run that reached the end of the previous chunk
-  uint32_t pending_key = kNoKey;
-  uint32_t prev_last = before;
-  for (int64_t c = s; c < e; c += kWave) {
-    const int n = (int)((e - c) < kWave ? (e - c) : kWave);
-    const bool last_chunk = c + kWave >= e;
-    uint32_t key = kNoKey;
-    Chunk ch;
-    ch.row = kBadRow;
-    ch.w = 0.0f;
-    ch.n = n;
-    if (lane < n) {
-      key = a.skeys[c + lane];
-      // unweighted pooling sorts bag ids with the keys; weighted pooling sorts
-      // positions (the weight is per position) and looks the bag up
-      const uint32_t sv = a.spos[c + lane];
-      const uint32_t pos = sv;
-      const int32_t g = a.sorted_bags ? (int32_t)sv : a.bag_of[pos];
-      const int64_t b = (int64_t)g - (int64_t)t * a.batch;
-      if (key >= kmin && key < sentinel && b >= 0 && b < a.batch) {
-        ch.row = (uint32_t)b;
-        if (a.coef == 1) {
-          ch.w = a.weights[pos];
-        } else if (a.coef == 2) {
-          const int64_t L = load_offset(a, g + 1) - load_offset(a, g);
-          ch.w = L > 0 ? 1.0f / (float)L : 0.0f;
-        } else {
-          ch.w = 1.0f;
+    for (int u = 0; u < Q; ++u) {
+#pragma unroll
+      for (int j = 0; j < P; ++j) {
+        const u32x4 x = load_grad(grads, ar[u], colb[j]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[u][4 * j + i] = __uint_as_float(x[i]);
+      }
+    }
+    float sq = 0.0f;  // of position q0 + sub, where sub < Q
+#pragma unroll
+    for (int u = 0; u < Q; ++u) {
+      const uint64_t at_u = every_group << (q0 + u);
+#pragma unroll
+      for (int i = 0; i < NV; ++i) acc[i] = fmaf(c[u], v[u][i], acc[i]);
+      if (upd & at_u) {
+        if (adagrad) {
+          const float x = square(acc);
+          sq = sub == u ? x : sq;
+        }
+        const bool up = (gupd >> (q0 + u)) & 1u;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+          v[u][i] = acc[i];
+          acc[i] = up ? 0.0f : acc[i];
+        }
+      }
+      if (hends & at_u) {
+        const bool hd = (ghead >> (q0 + u)) & 1u;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+          head[i] = hd ? acc[i] : head[i];
+          acc[i] = hd ? 0.0f : acc[i];
         }
       }
     }
-    const uint32_t up = (uint32_t)__shfl_up((int)key, 1);
-    const uint32_t prev = lane == 0 ? prev_last : up;
-    const uint64_t heads = __ballot(lane < n && key != prev);
-    // a run that ended exactly at the previous chunk's end
-    if (pending && (heads & 1ull)) {
-      finish(pending_key, false);
-      pending = false;
-    }
-    int a0 = 0;
-    if (!(heads & 1ull)) {
-      // the chunk opens inside a run: the pending one, or the tile's first
-      // run when it started in the previous tile
-      const int z = heads ? (int)__builtin_ctzll(heads) : n;
-      const uint32_t rkey = __builtin_amdgcn_readlane(key, 0);
-      if (!pending) start_run(rkey);
-      if (a.coef == 0) gather_range<kF32, LPR, false>(gm, a.ctx, ch, 0, z, acc, colb, colok);
-      else gather_range<kF32, LPR, true>(gm, a.ctx, ch, 0, z, acc, colb, colok);
-      if (z < n || last_chunk) {
-        finish(rkey, z == n);
-        pending = false;
-      } else {
-        pending = true;
-        pending_key = rkey;
+    if (updates) {
+      float scale = a.lr;
+      if (adagrad) {
+        float s_new;
+        scale = step_size(sq, s_old, s_new);
+        table.store_state(us, s_new);
       }
-      a0 = z;
-    }
-    if (a0 < n) {
-      // runs starting at heads: all but the last are complete inside this
-      // chunk and are updated here, several at once
-      const uint64_t hs = heads;
-      const int nheads = __builtin_popcountll(hs);
-      if (nheads > 1) {
-        short_runs<TDT, LPR>(a, m, gm, ch, key, hs, nheads - 1, starts);
-        first_run = false;
-      }
-      const int hl = 63 - __builtin_clzll(hs);
-      const uint32_t rkey = __builtin_amdgcn_readlane(key, hl);
-      start_run(rkey);
-      if (a.coef == 0) gather_range<kF32, LPR, false>(gm, a.ctx, ch, hl, n - hl, acc, colb, colok);
-      else gather_range<kF32, LPR, true>(gm, a.ctx, ch, hl, n - hl, acc, colb, colok);
-      if (last_chunk) {
-        finish(rkey, true);
-        pending = false;
-      } else {
-        pending = true;
-        pending_key = rkey;
+#pragma unroll
+      for (int u = 0; u < Q; ++u) {
+        if (upd & (every_group << (q0 + u))) update(ur[u], v[u], old[u], adagrad ? __shfl(scale, f + u) : scale);
       }
     }
-    prev_last = __builtin_amdgcn_readlane(key, n - 1);
+  }
+
+  // the runs that cross groups.  acc is the group's tail (if it has one);
+  // `whole`: the run covers the group, so the tail before it is added to it.
+  const bool ends_here = ghead != 0;  // a run that entered ends in this group
+  const uint32_t hrow = from_lane(row0, f);
+  const bool hvalid = __shfl((int)row_ok, f) != 0;
+  const addr_t hat = table.row_at(ends_here && hvalid, hrow);
+  const addr_t hstate = table.state_at(ends_here && hvalid && sub == 0, hrow);
+  slice_t hold[S];
+  float hs_old = 0.0f;
+  if (hends) {
+#pragma unroll
+    for (int j = 0; j < S; ++j) hold[j] = table.load(hat, tcolb[j]);
+    if (adagrad) hs_old = table.load_state(hstate);
+  }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) acc[i] = tail ? acc[i] : 0.0f;
+  bool whole = tail && gstarts == 0;
+#pragma unroll
+  for (int d = 1; d < G; d <<= 1) {
+    const bool from = whole && grp >= d;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const float x = __shfl_up(acc[i], d * LG);
+      acc[i] = from ? acc[i] + x : acc[i];
+    }
+    const bool o = __shfl_up((int)whole, d * LG) != 0;
+    whole = whole && (grp < d || o);
+  }
+  // now acc is the sum of the run that leaves the group, from the group it
+  // started in (or the wavefront's first) on; whole: it came from before the wavefront
+  constexpr int WV = LG * NV;  // values of a gradient row, padded
+  if (grp == G - 1) {
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s_sum[wave * WV + 4 * (sub + LG * j) + i] = acc[4 * j + i];
+    }
+    if (sub == LG - 1) s_flag[wave] = whole ? 1u : 0u;
+  }
+  __syncthreads();
+  // what enters this wavefront: the sum of the run that left the one before
+  float into[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) into[i] = 0.0f;
+  bool tile_entered = true;  // ... and whether it reaches back to the tile's start
+  for (int q = wave - 1; q >= 0; --q) {
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) into[4 * j + i] += s_sum[q * WV + 4 * (sub + LG * j) + i];
+    }
+    if (!__builtin_amdgcn_readfirstlane(s_flag[q])) {
+      tile_entered = false;
+      break;
+    }
+  }
+  // the sum of the run that leaves the tile
+  if (wave == waves - 1 && grp == G - 1 && tail) {
+    const bool entered = whole && tile_entered;
+    gf32 *slot = (gf32 *)a.carry + ((int64_t)2 * w + (entered ? 0 : 1)) * a.max_dim;
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+      if (cok[j]) {
+        float x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = acc[4 * j + i] + (whole ? into[4 * j + i] : 0.0f);
+        store_vals<kF32>((growb *)slot, col(j), x);
+      }
+    }
+  }
+  // the runs that entered a group and end in it
+  {
+    const bool whole_before = __shfl_up((int)whole, LG) != 0;  // (every lane takes part)
+    const bool from_wave = grp == 0 || whole_before;  // ... from before the wavefront
+    float x[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const float before = __shfl_up(acc[i], LG);
+      x[i] = (grp > 0 ? before : 0.0f) + (from_wave ? into[i] : 0.0f) + head[i];
+    }
+    const bool carried = from_wave && tile_entered;
+    if (ends_here && hvalid && carried) {
+      gf32 *slot = (gf32 *)a.carry + (int64_t)2 * w * a.max_dim;
+#pragma unroll
+      for (int j = 0; j < P; ++j) {
+        if (cok[j]) {
+          const float y[4] = {x[4 * j], x[4 * j + 1], x[4 * j + 2], x[4 * j + 3]};
+          store_vals<kF32>((growb *)slot, col(j), y);
+        }
+      }
+    }
+    if (hends) {
+      float scale = a.lr;
+      if (adagrad) {
+        float s_new;
+        scale = step_size(square(x), hs_old, s_new);
+        table.store_state(table.state_at(ends_here && hvalid && sub == 0 && !carried, hrow), s_new);
+        scale = __shfl(scale, f);
+      }
+      update(table.row_at(ends_here && hvalid && !carried, hrow), x, hold, scale);
+    }
   }
 }
 
-#define EB_BWD_LPR(LOG2)                                                        \
-  case LOG2:                                                                    \
-    tile_body<TDT, (1 << (LOG2))>(a, m, t, w, w - a.tile_start[t], starts);     \
+#define EB_BWD_LPR(LOG2)                                                                    \
+  case LOG2:                                                                                \
+    tile_body<TDT, (1 << (LOG2)), BIG>(a, m, t, w, w - a.tile_start[t], s_sum, s_flag);     \
     break;
-
-// Wavefronts per tiles-kernel workgroup.  A tile's time varies several-fold
-// with its runs (a chunk of single-occurrence rows takes many rounds, a piece
-// of a hot row's run one gather); one-wavefront workgroups let a finished
-// wavefront's slot take the next tile at once, where a four-wavefront
-// workgroup waits for a free slot on every SIMD (measured 3-5% faster).
-constexpr int kTileWaves = 1;
 
 // Tiles are numbered table by table; with XCD-contiguous workgroup order each
 // XCD walks one eighth of the tables, so its L2 keeps those tables' gradient
 // rows (B x D fp32 per table, re-read by every run of the table) instead of
 // all eight XCDs pulling the same table's gradient through the fabric.
-template <int TDT, int LOG2>
-__global__ __launch_bounds__(kWave * kTileWaves) void eb_bwd_tiles_kernel(BwdArgs a) {
-  const uint32_t blk = a.xcd_remap ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
-  const int32_t w = (int32_t)blk * kTileWaves + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+template <int TDT, int LOG2, bool BIG>
+__global__ __launch_bounds__(kWave * kMaxTileWaves) void eb_bwd_tiles_kernel(BwdArgs a) {
+  __shared__ float s_sum[kMaxTileWaves * kMaxBackwardDim];
+  __shared__ uint32_t s_flag[kMaxTileWaves];
+  const int32_t w = (int32_t)(a.xcd_remap ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x);
   if (w >= a.tile_start[a.num_tables]) return;
   const int32_t t = table_of_tile(a, w);
-  const TableMeta m = a.meta[t];
+  const TableMeta m = table_meta(a.meta, t);
   if (m.kind / 8 != TDT) return;
-  __shared__ int run_starts[kTileWaves][kWave + 1];
-  int *starts = run_starts[threadIdx.x / kWave];
   if constexpr (LOG2 >= 0) {
-    tile_body<TDT, (1 << LOG2)>(a, m, t, w, w - a.tile_start[t], starts);
+    tile_body<TDT, (1 << (LOG2)), BIG>(a, m, t, w, w - a.tile_start[t], s_sum, s_flag);
   } else {
     switch (log2_lanes_per_row(4 * m.dim)) {
       EB_BWD_LPR(0) EB_BWD_LPR(1) EB_BWD_LPR(2) EB_BWD_LPR(3) EB_BWD_LPR(4) EB_BWD_LPR(5) EB_BWD_LPR(6)
@@ -1058,7 +1232,7 @@ __global__ __launch_bounds__(kBlock) void eb_bwd_fixup_kernel(BwdArgs a) {
   };
   // Issued before the run's end is known: the row and its state, this
   // tile's partial and that of tile w + 1, which is always in the run.
-  const RowPrefetch<TDT, 4> pre = prefetch_row<TDT, 4>(m, a, (int64_t)(key - m.key_base), own, col);
+  const RowPrefetch pre = prefetch_row<TDT>(m, a, (int64_t)(key - m.key_base), own, col);
   f32x4 tail = {0.0f, 0.0f, 0.0f, 0.0f}, next = {0.0f, 0.0f, 0.0f, 0.0f};
   if (own) {
     tail = *(EB_GLOBAL const f32x4 *)((gf32 *)a.carry + ((int64_t)2 * w + 1) * a.max_dim + col);
@@ -1122,23 +1296,28 @@ __global__ __launch_bounds__(kBlock) void eb_bwd_fixup_kernel(BwdArgs a) {
       for (int i = 0; i < 4; ++i) g[i] += o[i];
     }
   }
-  apply_update<TDT, 4>(m, a, (int64_t)(key - m.key_base), g, own, col, pre);
+  apply_update<TDT>(m, a, (int64_t)(key - m.key_base), g, own, col, pre);
 }
 
 typedef void (*KernelFn)(BwdArgs);
 
-template <int TDT>
+template <int TDT, bool BIG>
 KernelFn pick_tiles(int log2) {
   switch (log2) {
-    case 0: return eb_bwd_tiles_kernel<TDT, 0>;
-    case 1: return eb_bwd_tiles_kernel<TDT, 1>;
-    case 2: return eb_bwd_tiles_kernel<TDT, 2>;
-    case 3: return eb_bwd_tiles_kernel<TDT, 3>;
-    case 4: return eb_bwd_tiles_kernel<TDT, 4>;
-    case 5: return eb_bwd_tiles_kernel<TDT, 5>;
-    case 6: return eb_bwd_tiles_kernel<TDT, 6>;
-    default: return eb_bwd_tiles_kernel<TDT, -1>;
+    case 0: return eb_bwd_tiles_kernel<TDT, 0, BIG>;
+    case 1: return eb_bwd_tiles_kernel<TDT, 1, BIG>;
+    case 2: return eb_bwd_tiles_kernel<TDT, 2, BIG>;
+    case 3: return eb_bwd_tiles_kernel<TDT, 3, BIG>;
+    case 4: return eb_bwd_tiles_kernel<TDT, 4, BIG>;
+    case 5: return eb_bwd_tiles_kernel<TDT, 5, BIG>;
+    case 6: return eb_bwd_tiles_kernel<TDT, 6, BIG>;
+    default: return eb_bwd_tiles_kernel<TDT, -1, BIG>;
   }
+}
+
+KernelFn pick_tiles(int dt, int log2, bool big) {
+  if (dt == kF32) return big ? pick_tiles<kF32, true>(log2) : pick_tiles<kF32, false>(log2);
+  return big ? pick_tiles<kF16, true>(log2) : pick_tiles<kF16, false>(log2);
 }
 
 // The workspace of eb_backward_update_noalloc: a static device array, one
@@ -1255,13 +1434,14 @@ unsigned bit_width(uint64_t x) {
 }
 
 eb_status layout(const eb_tables *h, int64_t n, BwdLayout *L) {
-  // Tiles of 64 positions keep short workloads spread over many wavefronts;
-  // from about two million positions on, tiles of 128 carry fewer partial
-  // sums (measured: 256 was slower at every size).
+  // A tile is 64 positions per wavefront of its workgroup.  The workspace has
+  // room for tiles of 64 positions (128 from about two million on), which is
+  // what its size has always been; a call uses the part its tiles need.
   int64_t chunks = n / (64 * 16384);
   chunks = chunks < 1 ? 1 : (chunks > 2 ? 2 : chunks);
   if (h->bwd_tile_chunks > 0) chunks = h->bwd_tile_chunks;
-  L->tile_size = (int32_t)(64 * chunks);
+  const int64_t room = (n + 64 * chunks - 1) / (64 * chunks) + h->num_tables;
+  L->tile_size = kWave * (h->bwd_tile_chunks > 0 ? h->bwd_tile_chunks : kTileWaves);
   L->tiles_ub = (n + L->tile_size - 1) / L->tile_size + h->num_tables;
   // The sort: rows up to the largest table's sentinel (its row count), in as
   // few passes of at most 9 bits as cover them, split evenly.
@@ -1285,9 +1465,9 @@ eb_status layout(const eb_tables *h, int64_t n, BwdLayout *L) {
   L->tile_start = off;
   off += align256(4 * (size_t)(h->num_tables + 1));
   L->tile_info = off;
-  off += align256(8 * (size_t)L->tiles_ub);
+  off += align256(8 * (size_t)room);
   L->carry = off;
-  off += align256(4 * (size_t)2 * L->tiles_ub * h->max_dim);
+  off += align256(4 * (size_t)2 * room * h->max_dim);
   L->sblocks = off;
   off += align256(16 * (size_t)L->nblk_max);
   L->nblocks = off;
@@ -1485,7 +1665,8 @@ eb_status backward_update(const eb_tables *h, eb_tensor indices, eb_tensor offse
     e = hipGetLastError();
   }
   // 3. tiles: pool and update (the first tile of each table came with the keys)
-  const unsigned tgrid = (unsigned)((L.tiles_ub + kTileWaves - 1) / kTileWaves);
+  const unsigned tgrid = (unsigned)L.tiles_ub;
+  const bool big = h->big_tables || (int64_t)batch * h->sum_dim * 4 > kMaxBufferBytes;
   const unsigned fgrid = (unsigned)((L.tiles_ub + kWavesPerBlock - 1) / kWavesPerBlock);
   // one launch per storage type present; fixed row width when all tables share it
   int32_t glog2 = log2_lanes_per_row(4 * h->h_meta[0].dim);
@@ -1493,9 +1674,7 @@ eb_status backward_update(const eb_tables *h, eb_tensor indices, eb_tensor offse
     if (log2_lanes_per_row(4 * h->h_meta[t].dim) != glog2) glog2 = -1;
   for (int dt = 0; dt < 2 && e == hipSuccess; ++dt) {
     if (!(h->dtype_mask & (1 << dt))) continue;
-    hipLaunchKernelGGL(dt == kF32 ? pick_tiles<kF32>(glog2) : pick_tiles<kF16>(glog2), dim3(tgrid),
-                       dim3(kWave * kTileWaves), 0,
-                       h->stream, a);
+    hipLaunchKernelGGL(pick_tiles(dt, glog2, big), dim3(tgrid), dim3((unsigned)L.tile_size), 0, h->stream, a);
     e = hipGetLastError();
   }
   // 4. runs that cross tiles

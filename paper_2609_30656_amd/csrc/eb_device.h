@@ -38,8 +38,7 @@ constexpr int kMaxBagsPerWave = 32;
 // Wavefronts resident on a full MI355X (256 CUs x 4 SIMDs x 8 waves).
 constexpr int64_t kResidentWaves = 256 * 4 * 8;
 constexpr int64_t kTailGens = 4;  // default taper of the lookup's runs (sets of resident wavefronts)
-// The backward keeps one gradient row slice per lane: rows of up to 64 lanes
-// x 4 fp32 values.
+// The backward holds a gradient row in up to 32 lanes of 8 fp32 values.
 constexpr int kMaxBackwardDim = 256;
 // Handles with at most this many tables renumber workgroups XCD-contiguously.
 constexpr int32_t kRemapMaxTables = 32;
@@ -348,10 +347,10 @@ struct RowSource<DT, false> {
   __amdgpu_buffer_rsrc_t rows, words;
   uint32_t stride, sb_stride;
   __device__ __forceinline__ RowSource(const TableMeta &m, const GatherCtx &) : stride(m.row_stride), sb_stride(m.sb_stride) {
-    rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(m.data), 0, m.num_rows * (int)m.row_stride,
+    rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(m.data), 0, (int)((uint32_t)m.num_rows * m.row_stride),
                                              kBufferFlags);
     if constexpr (DT == kU8)
-      words = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(m.sb_base), 0, m.num_rows * (int)m.sb_stride,
+      words = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(m.sb_base), 0, (int)((uint32_t)m.num_rows * m.sb_stride),
                                                 kBufferFlags);
   }
   __device__ __forceinline__ RowAddr<false> locate(uint32_t row) const {
@@ -447,46 +446,6 @@ __device__ __forceinline__ void gather_rows_exact(int rem, const RowSource<DT, B
   }
 }
 
-// Gather steps [s0, s0 + N) of one chunk (RPL rows per step) and add them into
-// this lane's accumulators.  Straight-line code: a lane whose row does not
-// exist (past the chunk's end, outside the table, or a slice past the row's
-// end) reads the handle's all-zero row instead, which adds nothing, so no
-// branch separates a load from its use and the loads of all N steps are in
-// flight together.
-template <int DT, int LPR, bool W, bool SPLIT, int N>
-__device__ __forceinline__ void gather_steps(const TableMeta &m, const GatherCtx &a, const Chunk &k, int s0,
-                                             float (&acc)[Vals<DT>::n], float &cb, int colb, bool colok,
-                                             int base = 0) {
-  constexpr int RPL = kWave / LPR;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int grp = lane / LPR;
-  u32x4 v[N];
-  uint32_t sb[N];
-  float w[N];
-#pragma unroll
-  for (int u = 0; u < N; ++u) {
-    const int r = (s0 + u) * RPL + grp;  // entry of the range [base, base + k.n)
-    uint32_t row;
-    if constexpr (RPL == 1) {
-      row = __builtin_amdgcn_readlane(k.row, (base + s0 + u) & (kWave - 1));
-      if constexpr (W)
-        w[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(uint32_t, k.w),
-                                                                    (base + s0 + u) & (kWave - 1)));
-    } else {
-      row = (uint32_t)__shfl((int)k.row, (base + r) & (kWave - 1));
-      if constexpr (W) w[u] = __shfl(k.w, (base + r) & (kWave - 1));
-    }
-    const bool ok = (r < k.n) && (row != kBadRow) && colok;
-    gbyte *p = ok ? (gbyte *)m.data + (uint64_t)row * m.row_stride : (gbyte *)a.zero;
-    v[u] = load_slice<DT>(p + colb);
-    if constexpr (DT == kU8) sb[u] = *reinterpret_cast<const EB_GLOBAL uint32_t *>(ok ? sb_word(m, row) : p);
-    else sb[u] = 0u;
-    if constexpr (!W) w[u] = 1.0f;
-  }
-#pragma unroll
-  for (int u = 0; u < N; ++u) accumulate<DT, W, SPLIT>(acc, cb, v[u], sb[u], w[u], a.one);
-}
-
 // Gather all rows of one chunk: full batches of U steps, then one batch for
 // the rest, so a chunk of up to U steps costs one memory round trip.  With
 // batches of 8 the last one has exactly the remaining steps: padding it to a
@@ -523,54 +482,6 @@ __device__ __forceinline__ void gather_chunk(const TableMeta &m, const GatherCtx
     }
     if (rem > 0) gather_rows<DT, LPR, W, SPLIT, 1, BIG>(src, at, a, k.w, s, acc, cb, colb);
   }
-}
-
-// One straight-line batch of exactly `rem` steps of entries from `base` on.
-template <int DT, int LPR, bool W, int N>
-__device__ __forceinline__ void gather_exact_at(int rem, const TableMeta &m, const GatherCtx &a, const Chunk &k, int s,
-                                                float (&acc)[Vals<DT>::n], float &cb, int colb, bool colok,
-                                                int base) {
-  if constexpr (N > 0) {
-    if (rem == N) {
-      gather_steps<DT, LPR, W, false, N>(m, a, k, s, acc, cb, colb, colok, base);
-      return;
-    }
-    gather_exact_at<DT, LPR, W, N - 1>(rem, m, a, k, s, acc, cb, colb, colok, base);
-  }
-}
-
-// Gather entries [base, base + n) of a chunk (n <= 64 - base) and accumulate
-// them: the same batching as gather_chunk, for a run that covers only part
-// of the chunk.
-template <int DT, int LPR, bool W>
-__device__ __forceinline__ void gather_range(const TableMeta &m, const GatherCtx &a, Chunk k, int base, int n,
-                                             float (&acc)[Vals<DT>::n], int colb, bool colok) {
-  constexpr int RPL = kWave / LPR;
-  constexpr int U = GatherUnroll<DT, RPL, W>::u;
-  float cb = 0.0f;
-  k.n = n;
-  const int steps = (n + RPL - 1) / RPL;
-  int s = 0;
-  if constexpr (U >= 8) {
-    for (; steps - s >= U; s += U) gather_steps<DT, LPR, W, false, U>(m, a, k, s, acc, cb, colb, colok, base);
-    if (steps > s) gather_exact_at<DT, LPR, W, U - 1>(steps - s, m, a, k, s, acc, cb, colb, colok, base);
-    return;
-  }
-  for (; steps - s > U / 2; s += U) gather_steps<DT, LPR, W, false, U>(m, a, k, s, acc, cb, colb, colok, base);
-  const int rem = steps - s;
-  if constexpr (U >= 8) {
-    if (rem > 2) {
-      gather_steps<DT, LPR, W, false, 4>(m, a, k, s, acc, cb, colb, colok, base);
-      return;
-    }
-  }
-  if constexpr (U >= 4) {
-    if (rem > 1) {
-      gather_steps<DT, LPR, W, false, 2>(m, a, k, s, acc, cb, colb, colok, base);
-      return;
-    }
-  }
-  if (rem > 0) gather_steps<DT, LPR, W, false, 1>(m, a, k, s, acc, cb, colb, colok, base);
 }
 
 __device__ __forceinline__ float dpp_row_ror(float x, int o) {
