@@ -628,7 +628,6 @@ typedef EB_GLOBAL unsigned char growb;
 typedef EB_GLOBAL float gf32;
 typedef EB_GLOBAL _Float16 gf16;
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 

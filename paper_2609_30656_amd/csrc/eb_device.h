@@ -118,6 +118,8 @@ __device__ __forceinline__ TableMeta table_meta(const TableMeta *meta, int32_t t
 }
 // same vector, only 4-byte aligned: int8 rows of D+4 bytes start on any dword
 typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 template <int DT>
@@ -224,6 +226,13 @@ struct GatherUnroll {
 __device__ __forceinline__ int64_t readlane64(int64_t v, int l) {
   const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, l);
   const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)((uint64_t)v >> 32), l);
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// A value every lane shares, in scalar registers.
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
@@ -362,6 +371,12 @@ struct RowSource<DT, false> {
   __device__ __forceinline__ u32x4 load_row(uint32_t at, int colb) const {
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, at + (uint32_t)colb, 0, 0));
   }
+  __device__ __forceinline__ u32x2 load_row8(uint32_t at, int colb) const {
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rows, at + (uint32_t)colb, 0, 0));
+  }
+  __device__ __forceinline__ uint32_t load_row4(uint32_t at, int colb) const {
+    return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rows, at + (uint32_t)colb, 0, 0);
+  }
   __device__ __forceinline__ uint32_t load_word(uint32_t at) const {
     return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(words, at, 0, 0);
   }
@@ -380,6 +395,12 @@ struct RowSource<DT, true> {
   }
   __device__ __forceinline__ u32x4 load_row(uint64_t at, int colb) const {
     return load_slice<DT>((gbyte *)(at + (uint64_t)colb));
+  }
+  __device__ __forceinline__ u32x2 load_row8(uint64_t at, int colb) const {
+    return *(const EB_GLOBAL u32x2_a4 *)(at + (uint64_t)colb);
+  }
+  __device__ __forceinline__ uint32_t load_row4(uint64_t at, int colb) const {
+    return *(const EB_GLOBAL uint32_t *)(at + (uint64_t)colb);
   }
   __device__ __forceinline__ uint32_t load_word(uint64_t at) const { return *(const EB_GLOBAL uint32_t *)at; }
 };

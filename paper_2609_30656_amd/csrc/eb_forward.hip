@@ -256,11 +256,6 @@ __device__ __forceinline__ void agent_store(uint32_t *p, uint32_t v) {
 __device__ __forceinline__ uint32_t agent_add(uint32_t *p, uint32_t v) {
   return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ int64_t uniform64(int64_t v) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
 
 // Queue the run's bags of more than a.long_len lookups (bags [g0, g0 + nb),
 // offsets my_off as run_offsets gives them).  Returns the mask of the bags
