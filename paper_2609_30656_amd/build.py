@@ -1,4 +1,5 @@
-"""Build libeb.so (the HIP kernels and the C ABI) for gfx950 with hipcc.
+"""Build libeb.so (the HIP kernels and the C ABI) for gfx950 with hipcc, and
+_ebbind.so (the Python binding's marshalling) with the host compiler.
 
     python -m paper_2609_30656_amd.build
 """
@@ -17,6 +18,9 @@ GATHER_SRC = os.path.join(CSRC, "gather_ceiling.hip")
 GATHER_BIN = os.path.join(PKG, "gather_ceiling")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libeb.so")
+# the Python binding's marshalling of the hot calls (a CPython extension, host code)
+BIND_SRC = os.path.join(CSRC, "eb_bind.cpp")
+BIND = os.path.join(PKG, "_ebbind.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",
@@ -42,6 +46,28 @@ def build(verbose: bool = False, extra_flags=()) -> str:
     return LIB
 
 
+def build_bind(verbose: bool = False) -> str:
+    """Compile the CPython extension that marshals the hot calls (host code only)."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+
+    tmp = BIND + ".tmp"
+    abi = int(torch._C._GLIBCXX_USE_CXX11_ABI)
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={abi}", "-I", INCLUDE, "-I", sysconfig.get_paths()["include"]]
+    for p in include_paths():
+        cmd += ["-isystem", p]
+    cmd += [BIND_SRC, "-L", libs, "-lc10", "-ltorch_cpu", "-ltorch_python", "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, BIND)
+    return BIND
+
+
 def build_gather_ceiling(verbose: bool = False) -> str:
     """Compile the gather_ceiling measurement program next to libeb.so."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -57,5 +83,6 @@ def build_gather_ceiling(verbose: bool = False) -> str:
 
 if __name__ == "__main__":
     print(build(verbose=True))
+    print(build_bind(verbose=True))
     print(build_gather_ceiling(verbose=True))
     sys.exit(0)

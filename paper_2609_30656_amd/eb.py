@@ -5,10 +5,17 @@ turns torch tensors into the plain pointers and sizes the C ABI takes.  Every
 step of the lookups, the FM term and the backward runs in libeb's HIP
 kernels; torch only owns the device memory and the stream.  If libeb.so has not been built this module
 raises on first use: there is no other implementation to fall back to.
+
+The lookups, the FM term and the backward with a given workspace go through a
+CPython extension (_ebbind.so) when every argument is an exact torch.Tensor
+that passes the checks; every other call, and every error, takes the ctypes
+path below, which makes the same checks.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from typing import Optional, Sequence
 
@@ -16,6 +23,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libeb.so")
+BIND_PATH = os.path.join(_HERE, "_ebbind.so")
 
 # eb_status
 EB_OK = 0
@@ -67,11 +75,26 @@ class eb_tensor(ctypes.Structure):
 
 
 _lib = None
+_bind = None  # the extension, bound to _lib's entry points
+
+
+def _load_bind(lib: ctypes.CDLL):
+    """Load _ebbind.so and give it the loaded library's entry points."""
+    if not os.path.exists(BIND_PATH):
+        raise RuntimeError(f"_ebbind.so not found at {BIND_PATH}; build it with "
+                           "`python -c 'import __graft_entry__ as g; g.build()'`")
+    loader = importlib.machinery.ExtensionFileLoader("_ebbind", BIND_PATH)
+    bind = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_ebbind", BIND_PATH, loader=loader))
+    loader.exec_module(bind)
+    bind.bind(*[ctypes.cast(getattr(lib, f), ctypes.c_void_p).value
+                for f in ("eb_forward", "eb_forward_seq", "eb_fm_cross", "eb_forward_fm", "eb_backward_update",
+                          "eb_backward_update_noalloc")])
+    return bind
 
 
 def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     """Load libeb.so (once).  Raises if it is missing: build it first."""
-    global _lib
+    global _lib, _bind
     if _lib is None:
         if not os.path.exists(path):
             raise RuntimeError(f"libeb.so not found at {path}; build it with "
@@ -103,6 +126,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         lib.eb_backward_update_noalloc.argtypes = [ctypes.c_void_p, eb_tensor, eb_tensor, eb_tensor, ctypes.c_int,
                                                    eb_tensor, ctypes.c_int32, ctypes.c_float, ctypes.c_float,
                                                    eb_tensor]
+        _bind = _load_bind(lib)
         _lib = lib
     return _lib
 
@@ -120,6 +144,8 @@ class EbTables:
         self.stream = stream
         self.sum_dim = sum_dim
         self.device = device
+        # the extension's device number (-1: no tensor is on it)
+        self._index = device.index if device is not None and device.type == "cuda" and device.index is not None else -1
 
     @property
     def num_tables(self) -> int:
@@ -205,11 +231,13 @@ def _as_tensor(t: Optional[torch.Tensor], device: Optional[torch.device] = None)
 def eb_forward(tables: EbTables, indices: torch.Tensor, offsets: torch.Tensor,
                per_sample_weights: Optional[torch.Tensor], pooling, out: torch.Tensor) -> torch.Tensor:
     """Enqueue the pooled lookup on the handle's stream; returns `out`."""
-    lib = load_library()
+    lib = _lib or load_library()
     mode = POOLING[pooling] if isinstance(pooling, str) else int(pooling)
-    d = tables.device
-    st = lib.eb_forward(tables.ptr, _as_tensor(indices, d), _as_tensor(offsets, d),
-                        _as_tensor(per_sample_weights, d), mode, _as_tensor(out, d))
+    st = _bind.forward(tables.ptr, tables._index, indices, offsets, per_sample_weights, mode, out)
+    if st is NotImplemented:
+        d = tables.device
+        st = lib.eb_forward(tables.ptr, _as_tensor(indices, d), _as_tensor(offsets, d),
+                            _as_tensor(per_sample_weights, d), mode, _as_tensor(out, d))
     if st != EB_OK:
         raise EBError(st, "eb_forward")
     return out
@@ -218,8 +246,11 @@ def eb_forward(tables: EbTables, indices: torch.Tensor, offsets: torch.Tensor,
 def eb_forward_seq(tables: EbTables, indices: torch.Tensor, offsets: torch.Tensor, out: torch.Tensor) -> torch.Tensor:
     """Un-pooled lookup: every position's row as fp32 into out (table t's
     positions as a [N_t, D_t] block, blocks in table order); returns out."""
-    d = tables.device
-    st = load_library().eb_forward_seq(tables.ptr, _as_tensor(indices, d), _as_tensor(offsets, d), _as_tensor(out, d))
+    lib = _lib or load_library()
+    st = _bind.forward_seq(tables.ptr, tables._index, indices, offsets, out)
+    if st is NotImplemented:
+        d = tables.device
+        st = lib.eb_forward_seq(tables.ptr, _as_tensor(indices, d), _as_tensor(offsets, d), _as_tensor(out, d))
     if st != EB_OK:
         raise EBError(st, "eb_forward_seq")
     return out
@@ -227,8 +258,11 @@ def eb_forward_seq(tables: EbTables, indices: torch.Tensor, offsets: torch.Tenso
 
 def eb_fm_cross(tables: EbTables, pooled: torch.Tensor, fm_out: torch.Tensor) -> torch.Tensor:
     """FM cross term of each example of a pooled output [B, T*D] into fm_out [B]; returns fm_out."""
-    d = tables.device
-    st = load_library().eb_fm_cross(tables.ptr, _as_tensor(pooled, d), _as_tensor(fm_out, d))
+    lib = _lib or load_library()
+    st = _bind.fm_cross(tables.ptr, tables._index, pooled, fm_out)
+    if st is NotImplemented:
+        d = tables.device
+        st = lib.eb_fm_cross(tables.ptr, _as_tensor(pooled, d), _as_tensor(fm_out, d))
     if st != EB_OK:
         raise EBError(st, "eb_fm_cross")
     return fm_out
@@ -238,11 +272,13 @@ def eb_forward_fm(tables: EbTables, indices: torch.Tensor, offsets: torch.Tensor
                   per_sample_weights: Optional[torch.Tensor], pooling, out: torch.Tensor,
                   fm_out: torch.Tensor) -> torch.Tensor:
     """eb_forward, then eb_fm_cross on its output into fm_out [B]; returns fm_out."""
-    lib = load_library()
+    lib = _lib or load_library()
     mode = POOLING[pooling] if isinstance(pooling, str) else int(pooling)
-    d = tables.device
-    st = lib.eb_forward_fm(tables.ptr, _as_tensor(indices, d), _as_tensor(offsets, d),
-                           _as_tensor(per_sample_weights, d), mode, _as_tensor(out, d), _as_tensor(fm_out, d))
+    st = _bind.forward_fm(tables.ptr, tables._index, indices, offsets, per_sample_weights, mode, out, fm_out)
+    if st is NotImplemented:
+        d = tables.device
+        st = lib.eb_forward_fm(tables.ptr, _as_tensor(indices, d), _as_tensor(offsets, d),
+                               _as_tensor(per_sample_weights, d), mode, _as_tensor(out, d), _as_tensor(fm_out, d))
     if st != EB_OK:
         raise EBError(st, "eb_forward_fm")
     return fm_out
@@ -264,6 +300,12 @@ def eb_backward_workspace_size(tables: EbTables, num_indices: int) -> int:
     return int(n.value)
 
 
+def _choice(names: dict, value):
+    """A named or numbered option as the C ABI takes it; None if it is neither
+    (the ctypes path then raises its error)."""
+    return names.get(value) if isinstance(value, str) else value if isinstance(value, int) else None
+
+
 def eb_backward_update(tables: EbTables, indices: torch.Tensor, offsets: torch.Tensor,
                        per_sample_weights: Optional[torch.Tensor], pooling, grad_out: torch.Tensor,
                        optimizer="sgd", learning_rate: float = 0.01, eps: float = 1e-8,
@@ -276,8 +318,18 @@ def eb_backward_update(tables: EbTables, indices: torch.Tensor, offsets: torch.T
     has run on the handle's stream; when None, one is allocated on that
     stream (torch's allocator then reuses it only for work ordered after the
     step on the same stream)."""
-    lib = load_library()
+    lib = _lib or load_library()
     d = tables.device
+    mode, opt = _choice(POOLING, pooling), _choice(OPTIMIZERS, optimizer)
+    if mode is not None and opt is not None and type(workspace) is torch.Tensor and workspace.device == d and \
+            workspace.is_contiguous():
+        st = _bind.backward(tables.ptr, tables._index, indices, offsets, per_sample_weights, mode, grad_out, opt,
+                            float(learning_rate), float(eps), optimizer_state, workspace.data_ptr(),
+                            workspace.numel() * workspace.element_size())
+        if st is not NotImplemented:
+            if st != EB_OK:
+                raise EBError(st, "eb_backward_update")
+            return
     args = (_as_tensor(indices, d), _as_tensor(offsets, d), _as_tensor(per_sample_weights, d))
     g, st_t = _as_tensor(grad_out, d), _as_tensor(optimizer_state, d)
     if workspace is None:
@@ -304,8 +356,16 @@ def eb_backward_update_noalloc(tables: EbTables, indices: torch.Tensor, offsets:
     nothing (EB_ERR_UNSUPPORTED if the batch needs more than
     EB_NOALLOC_SCRATCH_BYTES of workspace).  Calls that overlap on one GPU
     race on that workspace."""
-    lib = load_library()
+    lib = _lib or load_library()
     d = tables.device
+    mode, opt = _choice(POOLING, pooling), _choice(OPTIMIZERS, optimizer)
+    if mode is not None and opt is not None:
+        st = _bind.backward_noalloc(tables.ptr, tables._index, indices, offsets, per_sample_weights, mode, grad_out, opt,
+                                    float(learning_rate), float(eps), optimizer_state)
+        if st is not NotImplemented:
+            if st != EB_OK:
+                raise EBError(st, "eb_backward_update_noalloc")
+            return
     args = (_as_tensor(indices, d), _as_tensor(offsets, d), _as_tensor(per_sample_weights, d))
     g, st_t = _as_tensor(grad_out, d), _as_tensor(optimizer_state, d)
     mode = POOLING[pooling] if isinstance(pooling, str) else int(pooling)
