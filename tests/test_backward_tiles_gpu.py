@@ -91,3 +91,30 @@ def test_gradient_past_4gib(dev):  # noqa: F811
         # one rounding to the storage type of values up to about 20, fp32 sums of up to L terms
         bound = np.abs(want[t].cpu().numpy()).max() * (2.0 ** -11 if tb.dtype == "f16" else L * 2.0 ** -24) + 1e-5
         assert err <= bound, (t, err, bound)
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("most", [3_000_000, 100_000, 300])
+def test_tables_of_every_pass_count(dev, monkeypatch, most, weighted):  # noqa: F811
+    """Tables whose rows take one to three sort passes, next to one whose rows
+    set the launch's: each starts at its own pass, with its own digit bits; an
+    index outside its table among them."""
+    say(f"[bwd] tables of up to {most} rows")
+    g = torch.Generator(device="cpu")
+    g.manual_seed(most)
+    sizes = [r for r in (1, 2, 3, 127, 128, 255, 256, 511, 512, 5000, 65535, 65536, 262143, 262144, most) if r <= most]
+    tables = [Table(torch.randn((r, 4), generator=g).to(dev), 4, "f32") for r in sizes]
+    B = 37
+    lens = torch.randint(0, 60, (len(sizes) * B,), generator=g)
+    off = torch.zeros(lens.numel() + 1, dtype=torch.int64)
+    torch.cumsum(lens, 0, out=off[1:])
+    parts = []
+    for t, r in enumerate(sizes):
+        n = int(lens[t * B:(t + 1) * B].sum())
+        i = torch.randint(0, r, (n,), generator=g)
+        i[torch.rand(n, generator=g) < 0.2] = r - 1
+        parts.append(i)
+    idx = torch.cat(parts)
+    w = torch.rand(idx.numel(), generator=g).to(dev) if weighted else None
+    run_and_check(Workload("passes", tables, B, idx.to(dev), off.to(dev), w, "sum", lens.to(dev)), dev,
+                  "rowwise_adagrad", label=f"passes, up to {most} rows")
