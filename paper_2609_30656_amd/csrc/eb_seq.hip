@@ -12,8 +12,8 @@
 // of the pooled lookup: each is one exact conversion (or one rounding for
 // int8 row-wise rows), so the output matches its definition bit for bit.
 //
-// Work map: a wavefront takes a span of 64*k consecutive positions (k = 1
-// unless EB_BAGS_PER_WAVE says otherwise).  It finds
+// Work map: a wavefront takes a span of 64*k consecutive positions (k = 1, or
+// 2 for the largest calls, unless EB_BAGS_PER_WAVE says otherwise).  It finds
 // the table of its first position once (the lanes test 64 tables' start
 // offsets at a time and sum the earlier tables' output sizes), then walks the
 // span as a stream of chunks of up to 64 positions inside one table, loading
@@ -29,6 +29,8 @@
 
 namespace eb {
 namespace {
+
+constexpr int64_t kTwoChunksMin = (int64_t)1 << 20;  // chunks of a call from which a wavefront takes two
 
 struct SeqArgs {
   const TableMeta *meta;
@@ -401,8 +403,15 @@ extern "C" eb_status eb_forward_seq(const eb_tables *h, eb_tensor indices, eb_te
   // wavefronts that end soon keep the writes of neighbouring rows close in
   // time.  About sqrt(chunks / resident wavefronts) chunks, the rule before,
   // were 1-10% slower (8 fp16 tables of 128 at batch 16 384: 415 us against
-  // 396; 16 int8 tables of 128, 8.7 M positions: 1 259 against 1 145).
-  const int64_t k = h->bags_per_wave > 0 ? h->bags_per_wave : 1;
+  // 396; 16 int8 tables of 128, 8.7 M positions: 1 259 against 1 145).  From
+  // about a million chunks on, the wavefronts' own set-up costs more than the
+  // distance of the writes and two chunks are as fast or faster (one, two,
+  // four chunks, ms: 140 M positions in 64 int8 tables of 128 20.3, 19.8, 20.1;
+  // in 32 fp32 tables of 64 10.37, 10.17, 10.24; in 32 fp16 tables of 64 9.20,
+  // 9.06, 9.29; 72 M in 64 int8 tables 10.74, 10.65, 10.87, in 32 fp16 tables of
+  // 128 9.93, 9.95, 10.03; 36 M in 64 int8 tables 5.32, 5.39, 5.51).
+  const int64_t chunks = (n + kWave - 1) / kWave;
+  const int64_t k = h->bags_per_wave > 0 ? h->bags_per_wave : (chunks >= kTwoChunksMin ? 2 : 1);
   a.span = (int32_t)(k * kWave);
   a.num_waves = (n + a.span - 1) / a.span;
 

@@ -42,3 +42,20 @@ def test_output_too_small(dev, short):  # noqa: F811
     ref = ebo_forward_seq(oracle_tables(w), w.indices.cpu().numpy(), w.offsets.cpu().numpy())
     whole = (n - short) // 64 * 64 - 64  # every row before the last that fits
     assert np.array_equal(buf[:whole].cpu().numpy().view(np.uint32), ref[:whole].view(np.uint32))
+
+
+@pytest.mark.parametrize("n", [(1 << 26) - 64, (1 << 26) - 63, (1 << 26) + 65])
+def test_two_chunks_per_wavefront(dev, n):  # noqa: F811
+    # the last size of one chunk per wavefront and the first of two, with a
+    # table's end inside a chunk; fp32 rows come out as they are stored
+    say(f"[seq] {n} positions")
+    tables = [torch.randn((1000, 4), device=dev) for _ in range(2)]
+    cut = n // 2 // 64 * 64 + 31
+    indices = torch.randint(0, 1000, (n,), device=dev, dtype=torch.int32)
+    offsets = torch.tensor([0, cut, n], device=dev, dtype=torch.int32)
+    out = torch.full((4 * n,), 7.0, device=dev)
+    with eb.eb_create_tables([(t, 4, "f32") for t in tables]) as h:
+        eb.eb_forward_seq(h, indices, offsets, out)
+        torch.cuda.synchronize()
+    for t, (a, b) in enumerate(((0, cut), (cut, n))):
+        assert torch.equal(out[4 * a:4 * b].view(-1, 4), tables[t][indices[a:b].long()])
