@@ -118,3 +118,13 @@ def test_tables_of_every_pass_count(dev, monkeypatch, most, weighted):  # noqa: 
     w = torch.rand(idx.numel(), generator=g).to(dev) if weighted else None
     run_and_check(Workload("passes", tables, B, idx.to(dev), off.to(dev), w, "sum", lens.to(dev)), dev,
                   "rowwise_adagrad", label=f"passes, up to {most} rows")
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 4), ("f32", 32), ("f16", 128), ("f32", 256)])
+def test_run_of_many_tiles(dev, dtype, D):  # noqa: F811
+    # runs that cover 64 tiles of 256 positions after their own, one more, the
+    # fix-up's first full batch of partials, and an odd rest of it
+    for tiles, rest in ((64, 1), (65, 1), (66, 200), (73, 255), (200, 3)):
+        runs = [100, 256 * tiles + rest, 30]
+        w = _workload(dev, [(dtype, D)], [runs], "sum", tiles % 2 == 0, 64, seed=tiles)
+        run_and_check(w, dev, "sgd", label=f"run over {tiles} tiles {dtype} D={D}")
